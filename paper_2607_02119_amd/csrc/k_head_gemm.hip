@@ -10,87 +10,162 @@
 //
 // bf16 heads run on the streaming kernel (k_stream.hip) up to 128 GEMM rows and
 // on the MFMA-regime kernel (k_mfma.hip) above; fp32 heads (true fp32
-// products, for the fp32 parity workload) run on a plain FMA kernel here.
+// products) run on the fp32 matrix instruction here.
 #include "gemm_common.h"
 
 namespace mcd {
 namespace {
 
-// Epilogue of an audio tile for GEMM rows g (even) and g+1 at column n.
-__device__ inline void emit_audio(const HeadView &hv, const StepView &sv, const int32_t *rows,
-                                  int g, float v0, float v1, int n) {
-  if (n >= hv.N || g >= sv.Mg) return;
-  if (hv.bias) {
-    const float b = hv.bias[n];
-    v0 += b;
-    v1 += b;
-  }
-  if (g < 2 * sv.n_pairs) {
-    const int p = g >> 1;
-    const int r = rows[g];
-    if (r < 0 || r >= sv.R) return;
-    const float w = sv.cfg_w[r];
-    const float T = sv.temperature[r];
-    float s = fmaf(w, v0, (1.0f - w) * v1);
-    if (T > 0.0f) s = s * (1.0f / T);
-    sv.scores[(size_t)p * hv.N + n] = s;
-    return;
-  }
-  for (int q = 0; q < 2; ++q) {
-    const int gg = g + q;
-    if (gg >= sv.Mg) break;
-    const int r = rows[gg];
-    if (r < 0 || r >= sv.R) continue;
-    const float T = sv.temperature[r];
-    float s = q ? v1 : v0;
-    if (T > 0.0f) s = s * (1.0f / T);
-    sv.scores[(size_t)(sv.n_pairs + (gg - 2 * sv.n_pairs)) * hv.N + n] = s;
-  }
-}
+// fp32 path: true fp32 products on the fp32 matrix instruction
+// (v_mfma_f32_16x16x4_f32: lane l holds row or column l % 16 at k = l / 16).
+//
+// A workgroup owns 16 MB rows and 16 NB columns; its four waves take the k16
+// groups of H in turn and their sums meet in LDS.  A lane loads 16 bytes, four
+// consecutive k of its row or column, so one load feeds four MFMAs (their k
+// order is permuted alike on both sides) and a load instruction reads whole
+// 64-byte segments; loads of four groups are in flight together, the first
+// weights before the plan is read.  Small heads (4 rows, 4096 columns, H 256)
+// are bound by that chain of latencies: this form takes it from 46 us (one
+// thread per column, walking its weight row in 4-byte loads) to 4.1 us.
+//
+// Rows and columns past the end repeat the last one and are not stored.  H
+// need not be a multiple of 16 or 4 and the buffers only need 4-byte
+// alignment: the last group is read element by element.
+typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kF32Groups = 4;              // k16 groups in flight per wave
+constexpr int kF32Waves = 4;
 
-// fp32 path (plain FMA, ascending h).  256 threads: 64 columns x 4 row lanes;
-// thread (c, y) computes column n0 + c for GEMM row pairs y, y+4, ...
-template <bool TEXT>
+template <int MB, int NB, bool TEXT>
 __global__ __launch_bounds__(256) void head_gemm_f32(HeadView hv, StepView sv) {
-  if (!plan_ok(sv)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(sv.status, (uint32_t)MCD_DEV_BAD_PLAN);
-    return;
-  }
+  constexpr int U = kF32Groups, BM = 16 * MB, BN = 16 * NB, CP = BN + 1;
+  __shared__ float part[kF32Waves][BM][CP];
+  __shared__ float4 rowp[BM / 2];
   const int32_t *rows = sv.plan + kPlanHeader + (TEXT ? sv.Mg : 0);
   const int M = TEXT ? sv.n_text : sv.Mg;
   const int N = TEXT ? hv.V_text : hv.N;
   const float *Wp = static_cast<const float *>(TEXT ? hv.W_text : hv.W);
   const float *X = static_cast<const float *>(sv.hidden);
   const int H = hv.H;
-  const int c = threadIdx.x & 63, y = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + c;
-  const bool col_ok = n < N;
-  const float *wrow = Wp + (size_t)(col_ok ? n : 0) * H;
-  auto dot = [&](int g) -> float {
-    const int r = rows[g];
-    if (r < 0 || r >= sv.R) {
-      atomicOr(sv.status, (uint32_t)MCD_DEV_BAD_PLAN);
-      return 0.0f;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n0 = blockIdx.x * BN, m0 = blockIdx.y * BM;
+  const int c = lane & 15, kq = 4 * (lane >> 4);
+  const int G = H / 16;                    // whole k16 groups
+
+  const float *wp[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) wp[j] = Wp + (size_t)min(n0 + 16 * j + c, N - 1) * H + kq;
+  floatx4 wv[U][NB];
+  auto load_w = [&](int g0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int g = g0 + u * kF32Waves;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        wv[u][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (g < G) wv[u][j] = *reinterpret_cast<const float4_a4 *>(wp[j] + 16 * g);
+      }
     }
-    const float *x = X + (size_t)r * H;
-    float acc = 0.0f;
-    for (int h = 0; h < H; ++h) acc = fmaf(x[h], wrow[h], acc);
-    return acc;
+  };
+  load_w(wave);
+
+  if (!plan_ok(sv)) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0)
+      atomicOr(sv.status, (uint32_t)MCD_DEV_BAD_PLAN);
+    return;
+  }
+  const float *xp[MB];
+  float xs[MB];                            // 0 for a row outside the batch
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int r = rows[min(m0 + 16 * i + c, M - 1)];
+    const bool ok = r >= 0 && r < sv.R;
+    if (!ok) atomicOr(sv.status, (uint32_t)MCD_DEV_BAD_PLAN);
+    xp[i] = X + (size_t)(ok ? r : 0) * H + kq;
+    xs[i] = ok ? 1.0f : 0.0f;
+  }
+  if constexpr (!TEXT) {
+    if (tid < BM / 2) rowp[tid] = pair_params(sv, rows, m0 + 2 * tid);
+  }
+
+  floatx4 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto multiply = [&](const floatx4 (&a)[MB], const floatx4 (&b)[NB]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+  };
+  for (int g0 = wave; g0 < G; g0 += U * kF32Waves) {
+    floatx4 xv[U][MB];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int g = g0 + u * kF32Waves;
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        xv[u][i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (g < G && xs[i] != 0.0f) xv[u][i] = *reinterpret_cast<const float4_a4 *>(xp[i] + 16 * g);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) multiply(xv[u], wv[u]);
+    load_w(g0 + U * kF32Waves);
+  }
+  if (16 * G < H && wave == G % kF32Waves) {   // the last, partial group
+    floatx4 a[MB], b[NB];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = 16 * G + kq + e < H;
+#pragma unroll
+      for (int i = 0; i < MB; ++i) a[i][e] = (in && xs[i] != 0.0f) ? xp[i][16 * G + e] : 0.0f;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) b[j][e] = in ? wp[j][16 * G + e] : 0.0f;
+    }
+    multiply(a, b);
+  }
+  // lane l holds rows 4 (l / 16) .. + 3 of column l % 16 of every block
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wave][16 * i + kq + r][16 * j + c] = acc[i][j][r];
+  __syncthreads();
+  auto sum = [&](int row, int col) __attribute__((always_inline)) {
+    float v = part[0][row][col];
+#pragma unroll
+    for (int w = 1; w < kF32Waves; ++w) v += part[w][row][col];
+    return v;
   };
   if constexpr (!TEXT) {
-    for (int g = 2 * y; g < M; g += 8) {
-      const float v0 = col_ok ? dot(g) : 0.0f;
-      const float v1 = (col_ok && g + 1 < M) ? dot(g + 1) : 0.0f;
-      emit_audio(hv, sv, rows, g, v0, v1, n);
+    for (int item = tid; item < BM / 2 * BN; item += 256) {
+      const int q = item / BN, col = item % BN, n = n0 + col;
+      if (n >= N || m0 + 2 * q >= M) continue;
+      const float b = hv.bias ? hv.bias[n] : 0.0f;
+      const float v0 = sum(2 * q, col) + b, v1 = sum(2 * q + 1, col) + b;
+      const float4 pr = rowp[q];
+      const int o0 = __float_as_int(pr.z), o1 = __float_as_int(pr.w);
+      if (o1 == -2) {
+        sv.scores[(size_t)o0 * N + n] = fmaf(pr.x, v0, (1.0f - pr.x) * v1) * pr.y;
+      } else {
+        if (o0 >= 0) sv.scores[(size_t)o0 * N + n] = v0 * pr.x;
+        if (o1 >= 0) sv.scores[(size_t)o1 * N + n] = v1 * pr.y;
+      }
     }
   } else {
-    // two 32-column parts per block: lanes 0-31 and 32-63
-    for (int g0 = 0; g0 < M; g0 += 4) {
-      const int g = g0 + y;
+    static_assert(BN == kTextPartCols, "one text part per workgroup and row");
+    for (int item = tid; item < BM * BN; item += 256) {   // 32 lanes per row
+      const int row = item / BN, col = item % BN, n = n0 + col, g = m0 + row;
       float bv = -INFINITY;
       int bi = INT32_MAX;
-      if (g < M && col_ok) {
-        bv = dot(g);
+      if (n < N) {
+        bv = sum(row, col);
         bi = n;
       }
       for (int off = 1; off < 32; off <<= 1) {
@@ -98,13 +173,28 @@ __global__ __launch_bounds__(256) void head_gemm_f32(HeadView hv, StepView sv) {
         const int oi = __shfl_xor(bi, off);
         better(bv, bi, ov, oi);
       }
-      const int part = blockIdx.x * 2 + (c >> 5);
-      if ((c & 31) == 0 && g < M && part < sv.text_parts) {
-        sv.text_val[(size_t)g * sv.text_parts + part] = bv;
-        sv.text_idx[(size_t)g * sv.text_parts + part] = bi;
+      if (col == 0 && g < M) {
+        sv.text_val[(size_t)g * sv.text_parts + blockIdx.x] = bv;
+        sv.text_idx[(size_t)g * sv.text_parts + blockIdx.x] = bi;
       }
     }
   }
+}
+
+// 16 columns per workgroup (a text part, 32, for the text head); as few row
+// blocks as hold the rows, up to 64 rows, and row tiles beyond.
+template <bool TEXT>
+hipError_t launch_f32(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
+  constexpr int NB = TEXT ? 2 : 1;
+  const unsigned tn = (unsigned)((N + 16 * NB - 1) / (16 * NB));
+  if (M <= 16)
+    hipLaunchKernelGGL((head_gemm_f32<1, NB, TEXT>), dim3(tn), dim3(256), 0, st, hv, sv);
+  else if (M <= 32)
+    hipLaunchKernelGGL((head_gemm_f32<2, NB, TEXT>), dim3(tn), dim3(256), 0, st, hv, sv);
+  else
+    hipLaunchKernelGGL((head_gemm_f32<4, NB, TEXT>), dim3(tn, (unsigned)((M + 63) / 64)),
+                       dim3(256), 0, st, hv, sv);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -114,10 +204,8 @@ hipError_t launch_head_gemm_part(const HeadView &hv, const StepView &sv, bool te
   const int M = text ? sv.n_text : sv.Mg;
   if (M == 0) return hipSuccess;
   if (hv.dtype == MCD_F32) {
-    const int N = text ? hv.V_text : hv.N;
-    if (text) hipLaunchKernelGGL(head_gemm_f32<true>, dim3((N + 63) / 64), dim3(256), 0, st, hv, sv);
-    else hipLaunchKernelGGL(head_gemm_f32<false>, dim3((N + 63) / 64), dim3(256), 0, st, hv, sv);
-    return hipGetLastError();
+    return text ? launch_f32<true>(hv, sv, M, hv.V_text, st)
+                : launch_f32<false>(hv, sv, M, hv.N, st);
   }
   return M <= 128 ? launch_stream_gemm(hv, sv, text, st) : launch_mfma_gemm(hv, sv, text, st);
 }
