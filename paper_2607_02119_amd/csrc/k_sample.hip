@@ -21,7 +21,9 @@
 // four consecutive ids 4g .. 4g + 3 (one 16-byte load each), so that one
 // Philox4x32 block serves a whole group from registers.
 //
-// Selection.  Every score s falls in a bin b = floor(16 (max - s)) (bins of
+// Selection.  A top-k cut usually goes through a short list of the ids above a
+// bound near the k-th score (topk_by_list), which one wave finishes.  Vectors
+// that it does not serve go through bins.  Every score s falls in a bin b = floor(16 (max - s)) (bins of
 // width 1/16 below the maximum, the last one open-ended); the bin index is
 // monotone in s, so a cut between bins is a cut in the (score desc, id asc)
 // order.  One histogram pass (counts for top-k, masses for top-p) finds the bin
@@ -185,6 +187,9 @@ struct DrawItem {
   float x[4];
 };
 
+// Groups of four ids the top-k list holds: two per lane of the wave that draws.
+constexpr int kListCap = 2 * kWave;
+
 template <int TPV>
 struct Smem {
   // a cut-bin element; unused slots hold a sentinel that is never ahead of
@@ -196,17 +201,26 @@ struct Smem {
     unsigned long long m;                // mass (top-p)
   };
   static constexpr int kDraw = TPV;      // kept groups dealt through the list (one per thread)
-  uint32_t cnt[kBins + 1];               // top-k bin counts
+  // radix buffers: three in turn, so that a digit pass has one barrier; a
+  // one-wave group has none and clears its only one in place
+  static constexpr int kHists = TPV == kWave ? 1 : 3;
   union {
+    uint32_t cnt[kBins + 1];             // top-k bin counts
     unsigned long long mh[kBins + 1];    // top-p bin masses (the last: the open bin)
-    unsigned long long hist[3][256];     // radix select (fallback)
+    unsigned long long hist[kHists][256];  // radix select (fallback)
     DrawItem draw[kDraw];                // kept groups, once the selection is done
+    struct {                             // top-k list: groups with a score above the bound
+      float4 x[kListCap];
+      int g[kListCap];
+      float tmax[TPV == kWave ? 4 : kThreads];   // thread maxima of a workgroup group
+    } list;
   } u;
   // elements of the cut bin (at most TPV)
   Entry le[TPV];
   uint32_t nkw[5];                       // the vector's noise key, from its first wave
   uint32_t keepbits[TPV];                // kept cut-bin elements, one bit per slot of a thread
   uint32_t lcount;
+  uint32_t ncount;                       // groups in the top-k list
   // reductions across the waves of a group (two slots, alternating, one barrier each)
   uint32_t ru[2][Grp<TPV>::kGW];
   unsigned long long r64[2][Grp<TPV>::kGW];
@@ -566,6 +580,13 @@ __device__ __forceinline__ uint64_t mass_of(float s, float mx) {
   return (uint64_t)ldexpf(expf(s - mx), 48);
 }
 
+// A value the compiler takes for a new one: what is computed from it is
+// computed again here and not held from an earlier use.
+__device__ __forceinline__ float fresh(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // ---- radix select (fallback) -----------------------------------------------
 // Cut of "take `target` units from the top" among the active elements (units:
 // 1 per element, or its fixed-point mass).  Result: keep every active element
@@ -580,7 +601,8 @@ struct Cut {
 
 // `pass` counts the digit passes done so far in this vector and selects the
 // rotating buffers; the buffers pass % 3 and (pass + 1) % 3 must be zero on
-// entry, and the two after the last one used are zero again on exit.
+// entry, and the two after the last one used are zero again on exit.  (One
+// wave: the only buffer is zero on entry and on exit.)
 template <int GPT, int TPV, bool MASS>
 __device__ __forceinline__ Cut radix_select(const float (&x)[4 * GPT], uint32_t active,
                                             float mx, uint64_t target, Smem<TPV> &sm,
@@ -589,15 +611,19 @@ __device__ __forceinline__ Cut radix_select(const float (&x)[4 * GPT], uint32_t 
   const int gt = Grp<TPV>::tid(), lane = lane_id();
   uint32_t prefix = 0, pmask = 0;
   uint64_t rem = target;
+#pragma clang loop unroll(disable)
   for (int shift = 24; shift >= 0; shift -= 8) {
-    unsigned long long *h = sm.u.hist[pass % 3];
+    constexpr int NH = Smem<TPV>::kHists;
+    unsigned long long *h = sm.u.hist[pass % NH];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      const uint32_t key = order_key(x[i]);
+      const float xi = fresh(x[i]);
+      const uint32_t key = order_key(xi);
       if (((active >> i) & 1) && (key & pmask) == prefix) {
         const uint32_t d = (key >> shift) & 255u;
-        atomicAdd(&h[d], MASS ? (unsigned long long)mass_of(x[i], mx) : 1ull);
+        atomicAdd(&h[d], MASS ? (unsigned long long)mass_of(xi, mx) : 1ull);
       }
+      if constexpr (MASS) __builtin_amdgcn_sched_barrier(0);   // one mass at a time
     }
     Grp<TPV>::sync();
     // every wave scans all 256 digits (lane l: digits 255-4l .. 252-4l)
@@ -610,7 +636,10 @@ __device__ __forceinline__ Cut radix_select(const float (&x)[4 * GPT], uint32_t 
     const uint64_t incl = wave_incl_add_u64(lsum);
     const uint64_t excl = incl - lsum;
     // clear the buffer of the pass after next (its last readers passed the barrier above)
-    for (int b = gt; b < 256; b += TPV) sm.u.hist[(pass + 2) % 3][b] = 0;
+    // (one wave: this pass's, whose reads come first in program order)
+    if constexpr (TPV == kWave) Grp<TPV>::sync();
+    for (int b = gt; b < 256; b += TPV) sm.u.hist[(pass + NH - 1) % NH][b] = 0;
+    if constexpr (TPV == kWave) Grp<TPV>::sync();
     ++pass;
     const uint64_t bal = __ballot(excl < rem && incl >= rem);
     if (bal == 0) return Cut{0u, false, 0, true};
@@ -651,23 +680,24 @@ __device__ __forceinline__ uint32_t apply_cut(const float (&x)[4 * GPT], uint32_
   uint32_t keep = 0, ties = 0;
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const uint32_t key = order_key(x[i]);
+    const uint32_t key = order_key(fresh(x[i]));
     const bool act = (active >> i) & 1;
     if (act && key >= c.lo && !(c.exact && key == c.lo)) keep |= 1u << i;
     if (act && c.exact && key == c.lo) ties |= 1u << i;
   }
   if (!c.exact) return keep;
-  uint64_t base = 0;
+  const uint32_t need = (uint32_t)(need_n < MCD_MAX_V ? need_n : MCD_MAX_V);   // of at most V ties
+  uint32_t base = 0;
 #pragma unroll
   for (int q = 0; q < GPT; ++q) {
     const uint32_t tq = (ties >> (4 * q)) & 0xFu;
     uint32_t total;
     const uint32_t before = grp_excl_scan_u32<TPV>((uint32_t)__popc(tq), total, sm, slot);
-    uint64_t rank = base + before;
+    uint32_t rank = base + before;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if ((tq >> j) & 1) {
-        if (rank < need_n) keep |= 1u << (4 * q + j);
+        if (rank < need) keep |= 1u << (4 * q + j);
         ++rank;
       }
     }
@@ -716,14 +746,13 @@ __device__ __forceinline__ int find_cut_bin(const T *h, uint64_t target, uint64_
   return b;
 }
 
+// Bin of slot i (-1: not active), recomputed in every pass rather than held:
+// the array would set this kernel's register count, and with it how many
+// vectors a compute unit works on at a time.
 template <int GPT>
-__device__ __forceinline__ void bins_of(const float (&x)[4 * GPT], uint32_t active, float mx,
-                                        int (&bin)[4 * GPT]) {
-#pragma unroll
-  for (int i = 0; i < 4 * GPT; ++i) {
-    const float d = (mx - x[i]) * kBinScale;   // monotone in x
-    bin[i] = ((active >> i) & 1) ? (d < (float)kBins ? (int)d : kBins) : -1;
-  }
+__device__ __forceinline__ int bin_of(const float (&x)[4 * GPT], uint32_t active, float mx, int i) {
+  const float d = (mx - fresh(x[i])) * kBinScale;   // monotone in x
+  return ((active >> i) & 1) ? (d < (float)kBins ? (int)d : kBins) : -1;
 }
 
 // id of register slot i of group thread t
@@ -795,17 +824,17 @@ __device__ __forceinline__ void rank_and_keep(Smem<TPV> &sm, int n, uint64_t nee
 // falls back to the radix select when the count exceeds TPV).
 template <int GPT, int TPV, bool MASS>
 __device__ __forceinline__ void list_bin(Smem<TPV> &sm, const float (&x)[4 * GPT],
-                                         const int (&bin)[4 * GPT], int bc, float mx) {
+                                         uint32_t active, int bc, float mx) {
   constexpr int EPL = 4 * GPT;
   const int gt = Grp<TPV>::tid();
   uint32_t c = 0;
 #pragma unroll
-  for (int i = 0; i < EPL; ++i) c += bin[i] == bc ? 1u : 0u;
+  for (int i = 0; i < EPL; ++i) c += bin_of<GPT>(x, active, mx, i) == bc ? 1u : 0u;
   if (c == 0) return;
   uint32_t pos = atomicAdd(&sm.lcount, c);
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    if (bin[i] == bc) {
+    if (bin_of<GPT>(x, active, mx, i) == bc) {
       if (pos < (uint32_t)TPV) sm.le[pos] = {x[i], id_of<TPV>(i, gt), MASS ? mass_of(x[i], mx) : 0ull};
       ++pos;
     }
@@ -824,7 +853,8 @@ __device__ __forceinline__ void clear_list(Smem<TPV> &sm, int n) {
 template <int TPV>
 __device__ __forceinline__ void zero_radix(Smem<TPV> &sm) {
   Grp<TPV>::sync();
-  for (int b = Grp<TPV>::tid(); b < 2 * 256; b += TPV) sm.u.hist[b / 256][b % 256] = 0;
+  constexpr int NZ = Smem<TPV>::kHists > 1 ? 2 : 1;
+  for (int b = Grp<TPV>::tid(); b < NZ * 256; b += TPV) sm.u.hist[b / 256][b % 256] = 0;
   Grp<TPV>::sync();
 }
 
@@ -845,10 +875,11 @@ __device__ __forceinline__ uint32_t radix_topp(const float (&x)[4 * GPT], uint32
   uint64_t need_n = 0;
   if (c.exact) {
     // every element tied at kappa carries the same mass q: the fewest reaching rem
-    uint64_t q = 0;
+    bool any = false;
 #pragma unroll
     for (int i = 0; i < 4 * GPT; ++i)
-      if (((active >> i) & 1) && order_key(x[i]) == c.lo) q = mass_of(x[i], mx);
+      any |= ((active >> i) & 1) && order_key(fresh(x[i])) == c.lo;
+    uint64_t q = any ? mass_of(key_to_float(c.lo), mx) : 0ull;
     // every nonzero q is the same value, so the halves reduce independently
     const uint64_t qhi = grp_max_u32<TPV>((uint32_t)(q >> 32), sm, slot);
     const uint64_t qlo = grp_max_u32<TPV>((uint32_t)q, sm, slot);
@@ -862,30 +893,31 @@ __device__ __forceinline__ uint32_t radix_topp(const float (&x)[4 * GPT], uint32
 template <int GPT, int TPV>
 __device__ __forceinline__ uint32_t select_topk(const float (&x)[4 * GPT], uint32_t active,
                                                 float mx, int top_k, Smem<TPV> &sm, int &slot,
-                                                int &pass, int V, bool &u_dirty) {
+                                                int &pass, int V) {
   constexpr int EPL = 4 * GPT;
   const int gt = Grp<TPV>::tid();
-  int bin[EPL];
-  bins_of<GPT>(x, active, mx, bin);
 #pragma unroll
-  for (int i = 0; i < EPL; ++i)
-    if (bin[i] >= 0 && bin[i] < kBins) atomicAdd(&sm.cnt[bin[i]], 1u);
+  for (int i = 0; i < EPL; ++i) {
+    const int b = bin_of<GPT>(x, active, mx, i);
+    if (b >= 0 && b < kBins) atomicAdd(&sm.u.cnt[b], 1u);
+  }
   Grp<TPV>::sync();
   uint64_t above, inbin;
-  const int bc = find_cut_bin(sm.cnt, (uint64_t)top_k, above, inbin, (uint64_t)V);
+  const int bc = find_cut_bin(sm.u.cnt, (uint64_t)top_k, above, inbin, (uint64_t)V);
   const uint64_t need = (uint64_t)top_k - above;
   uint32_t keep = 0;
   if (bc < kBins && need == inbin) {
 #pragma unroll
-    for (int i = 0; i < EPL; ++i)
-      if (bin[i] >= 0 && bin[i] <= bc) keep |= 1u << i;
+    for (int i = 0; i < EPL; ++i) {
+      const int b = bin_of<GPT>(x, active, mx, i);
+      if (b >= 0 && b <= bc) keep |= 1u << i;
+    }
     return keep;
   }
   if (bc == kBins || inbin > (uint64_t)TPV) {
-    u_dirty = true;
     return radix_topk<GPT, TPV>(x, active, top_k, sm, slot, pass);
   }
-  list_bin<GPT, TPV, false>(sm, x, bin, bc, 0.0f);
+  list_bin<GPT, TPV, false>(sm, x, active, bc, mx);
   Grp<TPV>::sync();
   rank_and_keep<TPV, false>(sm, (int)inbin, need, 0, 0);
   Grp<TPV>::sync();
@@ -894,33 +926,32 @@ __device__ __forceinline__ uint32_t select_topk(const float (&x)[4 * GPT], uint3
   sm.keepbits[gt] = 0;          // next use follows at least one group barrier
   if (gt == 0) sm.lcount = 0;
 #pragma unroll
-  for (int i = 0; i < EPL; ++i)
-    if (bin[i] >= 0 && bin[i] < bc) keep |= 1u << i;
+  for (int i = 0; i < EPL; ++i) {
+    const int b = bin_of<GPT>(x, active, mx, i);
+    if (b >= 0 && b < bc) keep |= 1u << i;
+  }
   return keep;
 }
 
 // top-p over the active set (the survivors of top-k); `mx` is their maximum.
-// The mass histogram is zero on entry unless `u_dirty` (top-k used the radix
-// buffers that share its storage).
+// The mass histogram shares its storage with top-k's.
 template <int GPT, int TPV>
 __device__ __forceinline__ uint32_t select_topp(const float (&x)[4 * GPT], uint32_t active,
                                                 float mx, float top_p, Smem<TPV> &sm, int &slot,
-                                                int &pass, bool u_dirty) {
+                                                int &pass) {
   constexpr int EPL = 4 * GPT;
   const int gt = Grp<TPV>::tid(), lane = lane_id();
-  if (u_dirty) {   // group-uniform
-    Grp<TPV>::sync();
-    for (int b = gt; b <= kBins; b += TPV) sm.u.mh[b] = 0;
-    Grp<TPV>::sync();
-  }
+  Grp<TPV>::sync();
+  for (int b = gt; b <= kBins; b += TPV) sm.u.mh[b] = 0;
+  Grp<TPV>::sync();
   // every active element adds its mass to its bin (the open bin included), so
   // the bins also give the total
-  int bin[EPL];
-  bins_of<GPT>(x, active, mx, bin);
   if constexpr (TPV == kWave) Grp<TPV>::sync();   // the clearing stores before the adds
 #pragma unroll
-  for (int i = 0; i < EPL; ++i)
-    if (bin[i] >= 0) atomicAdd(&sm.u.mh[bin[i]], (unsigned long long)mass_of(x[i], mx));
+  for (int i = 0; i < EPL; ++i) {
+    const int b = bin_of<GPT>(x, active, mx, i);
+    if (b >= 0) atomicAdd(&sm.u.mh[b], (unsigned long long)mass_of(x[i], mx));
+  }
   Grp<TPV>::sync();
   // every wave scans the bins: the total Z, the target ceil(p Z), the cut bin
   uint64_t v[8], lsum = 0;
@@ -951,7 +982,7 @@ __device__ __forceinline__ uint32_t select_topp(const float (&x)[4 * GPT], uint3
     }
     cum += vj;
   }
-  list_bin<GPT, TPV, true>(sm, x, bin, bc, mx);
+  list_bin<GPT, TPV, true>(sm, x, active, bc, mx);
   Grp<TPV>::sync();
   const int n = (int)sm.lcount;
   if (n > TPV) {
@@ -967,8 +998,10 @@ __device__ __forceinline__ uint32_t select_topp(const float (&x)[4 * GPT], uint3
   sm.keepbits[gt] = 0;
   if (gt == 0) sm.lcount = 0;
 #pragma unroll
-  for (int i = 0; i < EPL; ++i)
-    if (bin[i] >= 0 && bin[i] < bc) keep |= 1u << i;
+  for (int i = 0; i < EPL; ++i) {
+    const int b = bin_of<GPT>(x, active, mx, i);
+    if (b >= 0 && b < bc) keep |= 1u << i;
+  }
   return keep;
 }
 
@@ -995,34 +1028,40 @@ __device__ __forceinline__ int draw_nucleus(const float (&x)[4 * GPT], uint32_t 
                                             int &slot) {
   constexpr int EPL = 4 * GPT;
   const int gt = Grp<TPV>::tid();
+  // One block at a time (the barrier keeps the compiler from interleaving all
+  // of them, whose registers would cost a wave per SIMD).  A thread's ids
+  // ascend with the slot, so the first of equal candidates stays.
   float gn[EPL];
+  uint32_t mk = 0;
+  Cand c = {-INFINITY, INT32_MAX, -INFINITY};
 #pragma unroll
   for (int q = 0; q < GPT; ++q) {
     const U32x4 wd = noise_block(nk, (uint32_t)(q * TPV + gt));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) gn[4 * q + j] = gumbel_from_word(wd.w[j]);
-  }
-  uint32_t mk = 0;
-  Cand c = {-INFINITY, INT32_MAX, -INFINITY};
-#pragma unroll
-  for (int i = 0; i < EPL; ++i) {
-    if (!((active >> i) & 1)) continue;
-    const uint32_t key = order_key(x[i]);
-    mk = key > mk ? key : mk;
-    keep_cand(c, x[i] + gn[i], id_of<TPV>(i, gt), x[i]);
+    for (int j = 0; j < 4; ++j) {
+      const int i = 4 * q + j;
+      gn[i] = gumbel_from_word(wd.w[j]);
+      if (!((active >> i) & 1)) continue;
+      const uint32_t key = order_key(x[i]);
+      mk = key > mk ? key : mk;
+      keep_cand(c, x[i] + gn[i], id_of<TPV>(i, gt), x[i]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
   c = grp_max_and_best<TPV>(mk, c, sm, slot);
   // no orderable candidate (every score NaN): the lowest id
   if (c.id == INT32_MAX) return 0;
   if (!(top_p < 1.0f)) return c.id;
   const float mx = key_to_float(mk);
+  // The masses (three instructions) and ids are recomputed in each pass; held
+  // across the passes they would cost a wave per SIMD.
+  int gtv = gt;
   auto ahead = [&](int i, const Cand &o) __attribute__((always_inline)) {
-    const int id = id_of<TPV>(i, gt);
+    const int id = id_of<TPV>(i, gtv);
     return ((active >> i) & 1) && ((x[i] > o.x) | ((x[i] == o.x) & (id < o.id)));
   };
-  // fp32 mass, recomputed in each pass (three instructions) rather than held
   auto mass_f = [&](int i) __attribute__((always_inline)) {
-    return __builtin_amdgcn_exp2f((x[i] - mx) * 1.4426950408889634f);
+    return __builtin_amdgcn_exp2f((fresh(x[i]) - mx) * 1.4426950408889634f);
   };
   float zf = 0.0f, af = 0.0f;
   Cand nc = {-INFINITY, INT32_MAX, -INFINITY};
@@ -1032,7 +1071,7 @@ __device__ __forceinline__ int draw_nucleus(const float (&x)[4 * GPT], uint32_t 
     zf += m;
     if (ahead(i, c)) {
       af += m;
-      keep_cand(nc, x[i] + gn[i], id_of<TPV>(i, gt), x[i]);
+      keep_cand(nc, x[i] + gn[i], id_of<TPV>(i, gtv), x[i]);
     }
   }
   nc = grp_fsum2_and_best<TPV>(zf, af, nc, sm, slot);
@@ -1041,15 +1080,13 @@ __device__ __forceinline__ int draw_nucleus(const float (&x)[4 * GPT], uint32_t 
     bool inside = af < pz;
     if (fabsf(af - pz) <= margin) {
       // near the cut: the fixed-point rule, mass ahead of c < ceil(p Z)
-      // (one element after the other: the empty asm statements keep their
+      // (one element after the other: fresh() and the asm below keep their
       // order, so that the masses are not all live at once)
       uint64_t z = 0, a = 0;
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
         if (!((active >> i) & 1)) continue;
-        float xi = x[i];
-        asm volatile("" : "+v"(xi));
-        const uint64_t m = mass_of(xi, mx);
+        const uint64_t m = mass_of(fresh(x[i]), mx);
         z += m;
         if (ahead(i, c)) a += m;
         asm volatile("" : "+v"(z), "+v"(a));
@@ -1066,15 +1103,271 @@ __device__ __forceinline__ int draw_nucleus(const float (&x)[4 * GPT], uint32_t 
     c = nc;
     af = 0.0f;
     nc = {-INFINITY, INT32_MAX, -INFINITY};
+    asm volatile("" : "+v"(gtv));
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
       if (ahead(i, c)) {
         af += mass_f(i);
-        keep_cand(nc, x[i] + gn[i], id_of<TPV>(i, gt), x[i]);
+        keep_cand(nc, x[i] + gn[i], id_of<TPV>(i, gtv), x[i]);
       }
     }
     nc = grp_fsum_and_best<TPV>(af, nc, sm, slot);
   }
+}
+
+// ---- top-k through a short list -------------------------------------------------
+// The k-th largest of any 256 maxima of disjoint parts of a vector is a lower
+// bound of its k-th largest score.  So: take such maxima (one per thread of a
+// workgroup group, four per lane of a one-wave group), bisect between their
+// smallest and largest for a bound that at least k of them reach, and move the
+// groups of four ids with a score at or above it to a list, usually a few more
+// than k.  From there one wave finishes the vector with at most two groups per
+// lane: it draws their noise and tests the best candidate as the draw without
+// a top-k cut does, against its rank (top-k alone) or against the exact top-k
+// set and its fixed-point masses (top-k with top-p).
+//
+// Against the histogram of every score this reads each score twice (a maximum
+// and a comparison) instead of computing its key, its bin and an LDS add, and
+// needs two barriers instead of six.  It does not serve vectors whose list
+// overflows (k above about 100, heavy ties at the bound) or whose scores are
+// not finite: those take the bins below, which give the same token.
+__device__ __forceinline__ float max_nan(float a, float b) {   // NaN if either is
+  return __builtin_elementwise_maximum(a, b);
+}
+
+__device__ __forceinline__ float wave_max_nan(float x) {
+  wave_scan([&](auto c, auto m) __attribute__((always_inline)) {
+    constexpr int C = decltype(c)::value, RM = decltype(m)::value;
+    x = max_nan(x, __uint_as_float(dpp<C, RM>(__float_as_uint(-INFINITY), __float_as_uint(x))));
+  });
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+}
+
+__device__ __forceinline__ float wave_min(float x) {
+  wave_scan([&](auto c, auto m) __attribute__((always_inline)) {
+    constexpr int C = decltype(c)::value, RM = decltype(m)::value;
+    x = fminf(x, __uint_as_float(dpp<C, RM>(__float_as_uint(INFINITY), __float_as_uint(x))));
+  });
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+}
+
+// The best candidate over the wave, as seen by every lane.
+__device__ __forceinline__ Cand wave_best(Cand c) {
+  wave_scan([&](auto cc, auto m) __attribute__((always_inline)) {
+    constexpr int C = decltype(cc)::value, RM = decltype(m)::value;
+    const float ov = __uint_as_float(dpp<C, RM>(__float_as_uint(-INFINITY), __float_as_uint(c.s)));
+    const int oi = (int)dpp<C, RM>((uint32_t)INT32_MAX, (uint32_t)c.id);
+    const float ox = __uint_as_float(dpp<C, RM>(__float_as_uint(-INFINITY), __float_as_uint(c.x)));
+    keep_cand(c, ov, oi, ox);
+  });
+  c.s = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c.s), 63));
+  c.id = __builtin_amdgcn_readlane(c.id, 63);
+  c.x = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(c.x), 63));
+  return c;
+}
+
+// Lanes of the wave, over every element e of n per lane, where pred(e) holds.
+template <int n, class Pred>
+__device__ __forceinline__ int wave_count(Pred &&pred) {
+  int c = 0;
+#pragma unroll
+  for (int e = 0; e < n; ++e) c += __popcll(__ballot(pred(e)));
+  return c;
+}
+
+// The end of a vector by one wave: n groups of four ids in the list (1 <= n <=
+// HG * kWave, HG groups per lane), of which every score below `bound` is left out (at least
+// min(k, finite scores) scores are not); mx: the vector's maximum.
+template <int HG, int TPV>
+__device__ __forceinline__ int draw_from_list(Smem<TPV> &sm, int n, float bound, float mx,
+                                              int top_k, float top_p, const NoiseKey &nk) {
+  constexpr int E = 4 * HG;                // elements per lane
+  const int lane = lane_id();
+  float x[E], s[E];
+  int id[E];
+#pragma unroll
+  for (int h = 0; h < HG; ++h) {
+    const int i = h * kWave + lane;
+    float4 v = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    int g = 0;
+    if (i < n) {
+      v = sm.u.list.x[i];
+      g = sm.u.list.g[i];
+    }
+    const float vs[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      x[4 * h + j] = vs[j] >= bound ? vs[j] : -INFINITY;
+      id[4 * h + j] = 4 * g + j;
+    }
+    const U32x4 w = noise_block(nk, (uint32_t)g);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[4 * h + j] = x[4 * h + j] + gumbel_from_word(w.w[j]);
+  }
+  auto in = [&](int e) __attribute__((always_inline)) { return x[e] > -INFINITY; };
+  auto ahead = [&](int e, const Cand &o) __attribute__((always_inline)) {
+    return (x[e] > o.x) | ((x[e] == o.x) & (id[e] < o.id));
+  };
+  auto best = [&](auto &&pred) __attribute__((always_inline)) {
+    Cand c = {-INFINITY, INT32_MAX, -INFINITY};
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (pred(e)) keep_cand(c, s[e], id[e], x[e]);
+    return wave_best(c);
+  };
+  if (!(top_p < 1.0f)) {
+    // the best candidate with fewer than k scores ahead of it
+    Cand c = best(in);
+    for (;;) {   // strictly earlier in the score order every time
+      if (wave_count<E>([&](int e) { return ahead(e, c); }) < top_k) return c.id;
+      const Cand o = c;
+      c = best([&](int e) { return ahead(e, o); });
+    }
+  }
+  // the exact top-k set: the k-th largest order key, bit by bit below the bits
+  // that the bound and the maximum share (until exactly k keys are at or above
+  // it, which is soon), ties to the lowest ids
+  const int total = wave_count<E>(in);
+  const int want = top_k < total ? top_k : total;
+  uint32_t key[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) key[e] = in(e) ? order_key(x[e]) : 0u;
+  const uint32_t kmx = order_key(mx), kdiff = kmx ^ order_key(bound);
+  const int nb = kdiff ? 32 - __builtin_clz(kdiff) : 0;
+  uint32_t kap = nb < 32 ? (kmx >> nb) << nb : 0u;
+  int at = total;                          // keys at or above kap
+  for (int b = nb - 1; b >= 0 && at != want; --b) {
+    const uint32_t t = kap | (1u << b);
+    const int c = wave_count<E>([&](int e) { return key[e] >= t; });
+    if (c >= want) {
+      kap = t;
+      at = c;
+    }
+  }
+  int idlim = INT32_MAX;
+  if (at != want) {                        // ties at kap: the lowest ids of them
+    const int need = want - wave_count<E>([&](int e) { return key[e] > kap; });
+    idlim = 0;                             // ties with an id below it: fewer than need
+    for (int b = 11; b >= 0; --b) {
+      const int t = idlim | (1 << b);
+      if (wave_count<E>([&](int e) { return key[e] == kap && id[e] < t; }) < need) idlim = t;
+    }
+  }
+  uint64_t m[E], z = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const bool keep = in(e) && (key[e] > kap || (key[e] == kap && id[e] <= idlim));
+    if (!keep) x[e] = -INFINITY;
+    m[e] = keep ? mass_of(x[e], mx) : 0ull;
+    z += m[e];
+  }
+  z = readlane_u64(wave_incl_add_u64(z), 63);
+  uint64_t target = (uint64_t)ceil((double)top_p * (double)z);
+  if (target < 1) target = 1;
+  Cand c = best(in);
+  for (;;) {
+    uint64_t a = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) a += ahead(e, c) ? m[e] : 0ull;
+    a = readlane_u64(wave_incl_add_u64(a), 63);
+    const Cand o = c;
+    if (a < target) return o.id;
+    c = best([&](int e) { return ahead(e, o); });
+    if (c.id == INT32_MAX) return o.id;    // nothing ahead of it
+  }
+}
+
+// The token of a vector with a top-k cut (all threads of the group call), or
+// -1, for every thread, when the list does not serve it.  In a workgroup group
+// the first wave has the token and the others 0.  sm.ncount is zero on entry
+// (published by the barrier here).
+template <int GPT, int TPV>
+__device__ __forceinline__ int topk_by_list(const float (&x)[4 * GPT], int top_k, float top_p,
+                                            const NoiseKey &nk_in, Smem<TPV> &sm) {
+  const int gt = Grp<TPV>::tid(), lane = lane_id();
+  // 256 maxima of disjoint parts of the vector, four per lane
+  float m[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    m[j] = x[j];
+#pragma unroll
+    for (int q = 1; q < GPT; ++q) m[j] = max_nan(m[j], x[4 * q + j]);
+  }
+  if constexpr (TPV != kWave) {
+    sm.u.list.tmax[gt] = max_nan(max_nan(m[0], m[1]), max_nan(m[2], m[3]));
+    Grp<TPV>::sync();
+    const float4 t = *reinterpret_cast<const float4 *>(&sm.u.list.tmax[4 * lane]);
+    m[0] = t.x;
+    m[1] = t.y;
+    m[2] = t.z;
+    m[3] = t.w;
+  }
+  const float mx = wave_max_nan(max_nan(max_nan(m[0], m[1]), max_nan(m[2], m[3])));
+  float lo = INFINITY;                     // parts without a finite score do not count
+#pragma unroll
+  for (int j = 0; j < 4; ++j) lo = fminf(lo, m[j] > -INFINITY ? m[j] : INFINITY);
+  lo = wave_min(lo);
+  // NaN, +inf, nothing but -inf, or a range past fp32: not here
+  if (!(mx > -INFINITY && mx - lo <= 3.0e38f)) return -1;
+  float bound = -3.4028234664e38f;         // every finite score
+  if (wave_count<4>([&](int j) { return m[j] > -INFINITY; }) >= top_k) {
+    // at least k maxima reach `bound` throughout; eight halvings leave a few
+    // scores more than k above it
+    float hi = mx;
+    bound = lo;
+    for (int it = 0; it < 8; ++it) {
+      const float mid = bound + 0.5f * (hi - bound);
+      const int c = wave_count<4>([&](int j) { return m[j] >= mid; });
+      if (c >= top_k) bound = mid;
+      else hi = mid;
+      if (c == top_k) break;
+    }
+  }
+  // groups with a score at or above the bound, to the list
+  uint64_t has[GPT];
+  int cnt = 0;
+#pragma unroll
+  for (int q = 0; q < GPT; ++q) {
+    const float gm = fmaxf(fmaxf(x[4 * q], x[4 * q + 1]), fmaxf(x[4 * q + 2], x[4 * q + 3]));
+    has[q] = __ballot(gm >= bound);
+    cnt += __popcll(has[q]);
+  }
+  int base = 0;
+  if constexpr (TPV != kWave) {
+    if (lane == 0) base = (int)atomicAdd(&sm.ncount, (uint32_t)cnt);
+    base = __builtin_amdgcn_readfirstlane(base);
+  }
+#pragma unroll
+  for (int q = 0; q < GPT; ++q) {
+    const uint32_t lo32 = (uint32_t)has[q], hi32 = (uint32_t)(has[q] >> 32);
+    const int pos = base + (int)__builtin_amdgcn_mbcnt_hi(hi32, __builtin_amdgcn_mbcnt_lo(lo32, 0));
+    if (((has[q] >> lane) & 1) && pos < kListCap) {
+      sm.u.list.x[pos] = make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+      sm.u.list.g[pos] = q * TPV + gt;
+    }
+    base += __popcll(has[q]);
+  }
+  Grp<TPV>::sync();
+  const int n = TPV == kWave ? cnt : (int)sm.ncount;
+  if (n > kListCap) return -1;
+  NoiseKey nk = nk_in;
+  if constexpr (TPV != kWave) {
+    if (Grp<TPV>::wave() != 0) return 0;
+    nk = NoiseKey{sm.nkw[0], sm.nkw[1], sm.nkw[2], sm.nkw[3], sm.nkw[4]};
+  }
+  if (n <= kWave) return draw_from_list<1, TPV>(sm, n, bound, mx, top_k, top_p, nk);
+  return draw_from_list<2, TPV>(sm, n, bound, mx, top_k, top_p, nk);
+}
+
+// The bins, lists and flags of the selection below, cleared for their first use.
+template <int TPV>
+__device__ __forceinline__ void clear_selection(Smem<TPV> &sm) {
+  const int gt = Grp<TPV>::tid();
+  Grp<TPV>::sync();                        // the top-k list's readers are done
+  for (int b = gt; b <= kBins; b += TPV) sm.u.cnt[b] = 0;
+  sm.keepbits[gt] = 0;
+  set_sentinel<TPV>(sm.le[gt]);
+  if (gt == 0) sm.lcount = 0;
 }
 
 template <int GPT, int TPV>
@@ -1098,7 +1391,7 @@ __device__ __forceinline__ int select_and_draw(const StepView &sv, const float (
     uint32_t id = 0xFFFFFFFFu;
 #pragma unroll
     for (int i = 0; i < EPL; ++i)
-      if (((active >> i) & 1) && order_key(x[i]) == mk) {
+      if (((active >> i) & 1) && order_key(fresh(x[i])) == mk) {
         const uint32_t e = (uint32_t)id_of<TPV>(i, gt);
         id = e < id ? e : id;
       }
@@ -1110,11 +1403,10 @@ __device__ __forceinline__ int select_and_draw(const StepView &sv, const float (
   NoiseKey nk = nk_in;
   if constexpr (TPV != kWave) nk = NoiseKey{sm.nkw[0], sm.nkw[1], sm.nkw[2], sm.nkw[3], sm.nkw[4]};
   int pass = 0;
-  bool u_dirty = false;
   uint32_t kept = active;
   if (top_k > 0 && top_k < V)
-    kept = select_topk<GPT, TPV>(x, kept, mx, top_k, sm, slot, pass, V, u_dirty);
-  if (top_p < 1.0f) kept = select_topp<GPT, TPV>(x, kept, mx, top_p, sm, slot, pass, u_dirty);
+    kept = select_topk<GPT, TPV>(x, kept, mx, top_k, sm, slot, pass, V);
+  if (top_p < 1.0f) kept = select_topp<GPT, TPV>(x, kept, mx, top_p, sm, slot, pass);
   // Gumbel-max over the kept ids, one Philox block per group of four ids
   float bv = -INFINITY;
   int bi = INT32_MAX;
@@ -1164,8 +1456,13 @@ __device__ __forceinline__ int select_and_draw(const StepView &sv, const float (
 }
 
 // One vector per group of TPV threads: 256 / TPV vectors per workgroup.
+// Six waves per SIMD: a vector is mostly latency (row lookups, scores, the
+// noise key, reductions), so the kernel is as fast as many vectors are in
+// flight.  4096 vectors of 4096 ids (top-k 50): 30.9 us at four waves, 27.7 at
+// five, 26.9 at six, 27.5 at eight (which spills in every path); 8192 vectors
+// of 1024 ids: 18.1, 18.2, 17.0.  Two registers of the radix fallback spill.
 template <int GPT, int TPV>
-__global__ __launch_bounds__(kThreads) void sample_kernel(HeadView hv, StepView sv,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void sample_kernel(HeadView hv, StepView sv,
                                                           int with_text) {
   constexpr int EPL = 4 * GPT;
   constexpr int G = kThreads / TPV;
@@ -1176,14 +1473,7 @@ __global__ __launch_bounds__(kThreads) void sample_kernel(HeadView hv, StepView 
   const int vec = __builtin_amdgcn_readfirstlane((int)blockIdx.x * G + Grp<TPV>::index());
   const int n_audio = sv.Rs * hv.K;
   if (vec >= n_audio + (with_text ? sv.n_text : 0)) return;   // a whole group
-  // the histograms start at zero (published by the first group reduction)
-  for (int b = gt; b <= kBins; b += TPV) {
-    sm.cnt[b] = 0;
-    sm.u.mh[b] = 0;
-  }
-  sm.keepbits[gt] = 0;
-  set_sentinel<TPV>(sm.le[gt]);
-  if (gt == 0) sm.lcount = 0;
+  if (gt == 0) sm.ncount = 0;   // published by the first group barrier
   int slot = 0;
 
   const bool audio = vec < n_audio;
@@ -1264,11 +1554,28 @@ __global__ __launch_bounds__(kThreads) void sample_kernel(HeadView hv, StepView 
     const bool masked = hv.T_text < hv.V_text;
     float bv = -INFINITY, av = -INFINITY;
     int bi = INT32_MAX, ai = INT32_MAX;
-    for (int p = gt; p < sv.text_parts; p += TPV) {
-      const float v = sv.text_val[(size_t)j * sv.text_parts + p];
-      const int i = sv.text_idx[(size_t)j * sv.text_parts + p];
-      if (!masked || p < tparts) keep_better(bv, bi, v, i);
-      keep_better(av, ai, v, i);
+    // eight partials of a thread in flight at a time (the ids past the end are
+    // clamped, and kept out by their value)
+    constexpr int PU = 8;
+    const float *tv = sv.text_val + (size_t)j * sv.text_parts;
+    const int32_t *ti = sv.text_idx + (size_t)j * sv.text_parts;
+    for (int p0 = gt; p0 < sv.text_parts; p0 += PU * TPV) {
+      float v[PU];
+      int id[PU];
+#pragma unroll
+      for (int q = 0; q < PU; ++q) {
+        const int p = min(p0 + q * TPV, sv.text_parts - 1);
+        v[q] = tv[p];
+        id[q] = ti[p];
+      }
+#pragma unroll
+      for (int q = 0; q < PU; ++q) {
+        const int p = p0 + q * TPV;
+        if (p < sv.text_parts) {
+          if (!masked || p < tparts) keep_better(bv, bi, v[q], id[q]);
+          keep_better(av, ai, v[q], id[q]);
+        }
+      }
     }
     const int tok = grp_argmax_f32<TPV>(bv, bi, sm, slot);
     int leave = 0;
@@ -1314,7 +1621,11 @@ __global__ __launch_bounds__(kThreads) void sample_kernel(HeadView hv, StepView 
           nk = NoiseKey{sm.nkw[0], sm.nkw[1], sm.nkw[2], sm.nkw[3], sm.nkw[4]};
         token = draw_nucleus<GPT, TPV>(x, active, nk, P, sm, slot);
       } else {
-        token = select_and_draw<GPT, TPV>(sv, x, active, V, T == 0.0f, top_k, P, nk, sm, slot);
+        token = T != 0.0f ? topk_by_list<GPT, TPV>(x, top_k, P, nk, sm) : -1;
+        if (token < 0) {
+          clear_selection<TPV>(sm);
+          token = select_and_draw<GPT, TPV>(sv, x, active, V, T == 0.0f, top_k, P, nk, sm, slot);
+        }
       }
       sampled = true;
     }

@@ -62,3 +62,81 @@ def test_fp32_head_tiles(H, V, pairs, solo, text, V_text):
                          bias=H % 2 == 0)
     say(f"case {wl.name} R={wl.R}")
     check_one_step(wl, 2, 1e-5)
+
+
+# top-k through the short list: one group of ids per lane and two, the list's
+# capacity (128 groups) reached and passed, k above the parts that have a
+# score, masked ids, ties at the bound, with and without a nucleus; one
+# workgroup per vector and (from 1024 vectors of at most 1024 ids) one wave
+TOPK = [
+    # V, K, Rs, sigma, quantum, top_k, top_p, masked share, mask value
+    (2, 2, 3, 1.0, 0.0, 1, 1.0, 0.0, 0.0),
+    (5, 4, 256, 1.0, 0.0, 4, 0.9, 0.0, 0.0),
+    (255, 2, 5, 2.0, 0.0, 254, 0.95, 0.0, 0.0),
+    (513, 2, 5, 2.0, 0.0, 1, 0.5, 0.0, 0.0),
+    (4096, 2, 6, 3.6, 0.0, 64, 1.0, 0.0, 0.0),
+    (4096, 2, 6, 3.6, 0.0, 64, 0.9, 0.0, 0.0),
+    (4095, 2, 6, 3.6, 0.0, 110, 0.9, 0.0, 0.0),
+    (4096, 2, 6, 3.6, 0.0, 128, 1.0, 0.0, 0.0),
+    (4096, 2, 6, 3.6, 0.0, 256, 0.8, 0.0, 0.0),
+    (2048, 2, 6, 3.6, 0.125, 50, 1.0, 0.0, 0.0),
+    (2048, 2, 6, 3.6, 0.125, 50, 0.9, 0.0, 0.0),
+    (2048, 2, 6, 1.0, 1.0, 20, 0.9, 0.0, 0.0),
+    (4096, 2, 6, 2.0, 0.0, 50, 0.9, 0.99, -1e30),
+    (4096, 2, 6, 2.0, 0.0, 50, 1.0, 0.5, -3.0e38),
+    (1024, 4, 256, 3.6, 0.0, 64, 0.9, 0.0, 0.0),
+    (1024, 4, 256, 3.6, 0.0, 100, 1.0, 0.0, 0.0),
+    (1024, 4, 256, 3.6, 0.125, 40, 0.9, 0.0, 0.0),
+    (1003, 4, 256, 3.6, 0.0, 30, 0.9, 0.9, -1e30),
+    (130, 8, 128, 2.0, 0.0, 129, 0.99, 0.0, 0.0),
+]
+
+
+def sampler_only(V, K, Rs, top_k, top_p):
+    wl = inputs.Workload("sampler", H=64, K=K, V=V, n_pairs=0, n_solo=Rs, top_k=top_k,
+                         top_p=top_p, steps=3 * K)
+    return wl, harness.DeviceWorkload(wl, weights=dict(
+        H=64, K=K, V=V, pad_id=V, delays=np.arange(K, dtype=np.int32),
+        W=np.zeros((K, V, 64), np.uint16), bias=None, W_text=None))
+
+
+@pytest.mark.parametrize("V,K,Rs,sigma,quantum,top_k,top_p,share,value", TOPK)
+def test_topk_list_edges(V, K, Rs, sigma, quantum, top_k, top_p, share, value):
+    """The sampler alone on the same scores as the oracle; the exemptions are its own rounding:
+    top-2 gaps below 1e-4, nucleus cuts within 1e-6 of p; top-k cuts are exact."""
+    say(f"case V={V} K={K} Rs={Rs} top_k={top_k} top_p={top_p} q={quantum} masked={share}")
+    wl, dw = sampler_only(V, K, Rs, top_k, top_p)
+    tc = TokenCheck()
+    srow = [r for r, _ in dw.plan.sampled_rows()]
+    for t in (K - 1, K):
+        sc = inputs.make_scores(Rs, wl.N, t, sigma=sigma, quantum=quantum)
+        sc[np.random.default_rng(t).random(sc.shape) < share] = value
+        dw.tokens.fill_(-1)
+        dw.sample_only(t, harness.to_device(sc))
+        torch.cuda.synchronize()
+        o = oracle.sample_rows(dw.host_head, inputs.make_batch(wl, t, dw.layout), srow,
+                               [-1] * Rs, sc.astype(np.float64), gap_tol=1e-4, topk_tol=0.0,
+                               topp_tol=1e-6)
+        tc.add(dw.tokens.cpu().numpy(), o["tokens"], o["flags"], where=f"t={t}")
+    tc.assert_ok(f"V={V} k={top_k}")
+
+
+@pytest.mark.parametrize("V,K,Rs,top_p", [(4096, 4, 4, 1.0), (512, 8, 128, 0.9)])
+def test_topk_infinite_scores_give_valid_ids(V, K, Rs, top_p):
+    """Infinite scores with a top-k cut: a valid id, and a finite score's id wherever only some
+    scores are minus infinity."""
+    say(f"case infinite V={V} K={K} Rs={Rs}")
+    wl, dw = sampler_only(V, K, Rs, 20, top_p)
+    sc = inputs.make_scores(Rs, wl.N, 1, sigma=2.0)
+    sc[2, :V] = -np.inf
+    sc[3, :V:5] = np.inf
+    sc[0, V:2 * V] = -np.inf
+    sc[0, V + 11] = 1.0
+    sc[1, V:2 * V:2] = -np.inf
+    dw.tokens.fill_(-1)
+    dw.sample_only(K - 1, harness.to_device(sc))
+    torch.cuda.synchronize()
+    rows = [r for r, _ in dw.plan.sampled_rows()]
+    g = dw.tokens.cpu().numpy()[rows]
+    assert np.all((g >= 0) & (g < V))
+    assert g[0, 1] == 11 and g[1, 1] % 2 == 1
