@@ -284,30 +284,39 @@ __device__ __forceinline__ void dma_tile(const HeadView &hv, const StepView &sv,
     }
   }
 
-  // MFMAs of slice st, from its stages.  The fragments of the next k16 step
-  // are read while the MFMAs of this one run, and extra(m) (this wave's copy
-  // work for a later slice) is issued after MFMA m, so that the matrix pipe,
-  // the LDS and the load path work at once instead of in turn.
+  // One slice.  The fragments of a k16 step are read while the MFMAs of the
+  // step before it run, across slices too: the barrier that makes slice st + 1
+  // visible sits before the last step of slice st, whose fragments are in
+  // registers by then, and the first step of slice st + 1 is read during its
+  // MFMAs.  So no wave waits for an LDS read at the top of a slice, and the
+  // stage of slice st is free again one step before its MFMAs end.
+  // extra(m) (this wave's copy work for a later slice) is issued after MFMA m,
+  // so that the matrix pipe, the LDS and the load path work at once instead of
+  // in turn; arrive() is this wave's wait for what it copied of slice st + 1.
   constexpr int NMF = KS * MB * NB;        // MFMAs per wave and slice
-  auto compute = [&](int st, auto &&extra) __attribute__((always_inline)) {
+  constexpr int NPRE = (KS - 1) * MB * NB; // of them before the barrier
+  static_assert(KS % 2 == 0, "step 0 of the next slice goes to fragment buffer 0");
+  bf16x8 fa[2][MB], fb[2][NB];
+  auto read_step = [&](int st, auto sc) __attribute__((always_inline)) {
+    constexpr int s2 = decltype(sc)::value, buf = s2 & 1;
     const char *wsb = wring + (st % SW) * WST;
     const char *asb = aring + (st % SA) * AST;
-    bf16x8 fa[2][MB], fb[2][NB];
     static_for<0, MB>([&](auto ic) __attribute__((always_inline)) {
-      fa[0][ic] = *reinterpret_cast<const bf16x8 *>(asb + aoff[0][ic]);
+      fa[buf][ic] = *reinterpret_cast<const bf16x8 *>(asb + aoff[s2][ic]);
     });
     static_for<0, NB>([&](auto jc) __attribute__((always_inline)) {
-      fb[0][jc] = *reinterpret_cast<const bf16x8 *>(wsb + woff[0][jc]);
+      fb[buf][jc] = *reinterpret_cast<const bf16x8 *>(wsb + woff[s2][jc]);
     });
+  };
+  auto slice = [&](int st, auto &&extra, auto &&arrive) __attribute__((always_inline)) {
     static_for<0, KS>([&](auto sc) __attribute__((always_inline)) {
-      constexpr int s2 = decltype(sc)::value, cur = s2 & 1, nxt = cur ^ 1;
+      constexpr int s2 = decltype(sc)::value, cur = s2 & 1;
       if constexpr (s2 + 1 < KS) {
-        static_for<0, MB>([&](auto ic) __attribute__((always_inline)) {
-          fa[nxt][ic] = *reinterpret_cast<const bf16x8 *>(asb + aoff[s2 + 1][ic]);
-        });
-        static_for<0, NB>([&](auto jc) __attribute__((always_inline)) {
-          fb[nxt][jc] = *reinterpret_cast<const bf16x8 *>(wsb + woff[s2 + 1][jc]);
-        });
+        read_step(st, std::integral_constant<int, s2 + 1>{});
+      } else {
+        arrive();
+        block_barrier_no_vmem_wait();
+        read_step(st + 1, std::integral_constant<int, 0>{});   // past the end: never used
       }
       static_for<0, MB * NB>([&](auto mc) __attribute__((always_inline)) {
         constexpr int m = decltype(mc)::value, i = m / NB, j = m % NB;
@@ -318,57 +327,60 @@ __device__ __forceinline__ void dma_tile(const HeadView &hv, const StepView &sv,
     });
   };
   // The two roles run separate copies of the loop (one barrier per iteration
-  // in both), so that the hidden-state registers exist on one path only.
-  // At the top of iteration st: the weight waves' copies of slice st have
+  // in both), so that the hidden-state registers exist on one path only.  At
+  // the barrier of slice st: the weight waves' copies of slice st + 1 have
   // landed (those of later slices may still be in flight); every wave's LDS
-  // reads of slice st - 1 and writes of slice st are done.  The barrier
-  // extends both to the whole workgroup.
+  // reads of slice st and writes of slice st + 1 are done.  The barrier
+  // extends both to the whole workgroup.  The first one stands before the loop.
   if (w_copier) {
+    wait_slices<WIW, SW - 2>(NST - 1);
+    block_barrier_no_vmem_wait();
+    read_step(0, std::integral_constant<int, 0>{});
     for (int st = 0; st < NST; ++st) {
-      wait_slices<WIW, SW - 2>(NST - 1 - st);
-      block_barrier_no_vmem_wait();
       const int cs = st + SW - 1;        // the slice whose copies go out now
       const bool go = cs < NST;
       int ks = cs + kskew;
       ks = ks >= NST ? ks - NST : ks;
       const uint32_t sb = wbase + (uint32_t)((cs % SW) * WST);
-      compute(st, [&](auto mc) __attribute__((always_inline)) {
+      slice(st, [&](auto mc) __attribute__((always_inline)) {
         constexpr int m = decltype(mc)::value;
-        // copies q with q * NMF / WIW == m go out after MFMA m
+        // copies q with q * NPRE / WIW == m go out after MFMA m, all of them
+        // before the barrier, whose wait counts them
         static_for<0, WIW>([&](auto qc) __attribute__((always_inline)) {
           constexpr int q = decltype(qc)::value;
-          if constexpr (q * NMF / WIW == m) {
+          if constexpr (q * NPRE / WIW == m) {
             if (go) lds_copy16_stream(src[q] + ks * SK, sb + (uint32_t)((wave_s * WIW + q) * 1024));
           }
         });
+      }, [&]() __attribute__((always_inline)) {
+        wait_slices<WIW, SW - 2>(max(NST - 2 - st, 0));
       });
     }
   } else {
+    wait_vmem_and_lds<63>();
+    block_barrier_no_vmem_wait();
+    read_step(0, std::integral_constant<int, 0>{});
     // unrolled by HL, so that each register buffer has a fixed name: buffer j
     // holds the slices s with (s - SA + 1) % HL == j
     auto iteration = [&](int st, u32x4 (&hbj)[AIA]) __attribute__((always_inline)) {
-      wait_vmem_and_lds<63>();
-      block_barrier_no_vmem_wait();
       const int ss = st + SA - 1;        // stored now, into the stage read in iteration st - 1
       const bool sgo = ss < NST;
       char *sbase = aring + (ss % SA) * AST + ((wave_s - 2) * AIA) * 1024 + lane * 16;
       int ks = min(st + SA - 1 + HL, NST - 1) + kskew;
       ks = ks >= NST ? ks - NST : ks;
-      compute(st, [&](auto mc) __attribute__((always_inline)) {
+      slice(st, [&](auto mc) __attribute__((always_inline)) {
         constexpr int m = decltype(mc)::value;
-        // op o < AIA: store chunk o; op AIA + q: reload register q (after its store)
-        static_for<0, 2 * AIA>([&](auto oc) __attribute__((always_inline)) {
-          constexpr int o = decltype(oc)::value;
-          if constexpr (o * NMF / (2 * AIA) == m) {
-            if constexpr (o < AIA) {
-              if (sgo) *reinterpret_cast<u32x4 *>(sbase + o * 1024) = hbj[o];
-            } else {
-              constexpr int q = o - AIA;
-              hbj[q] = *reinterpret_cast<const u32x4 *>(src[q] + ks * SK);
-            }
+        // store chunk q before the barrier, reload its register after that
+        static_for<0, AIA>([&](auto qc) __attribute__((always_inline)) {
+          constexpr int q = decltype(qc)::value;
+          if constexpr (q * NPRE / AIA == m) {
+            if (sgo) *reinterpret_cast<u32x4 *>(sbase + q * 1024) = hbj[q];
+          }
+          if constexpr (q * NMF / AIA == m) {
+            hbj[q] = *reinterpret_cast<const u32x4 *>(src[q] + ks * SK);
           }
         });
-      });
+      }, [&]() __attribute__((always_inline)) { wait_vmem_and_lds<63>(); });
     };
     int st0 = 0;
     for (; st0 + HL <= NST; st0 += HL) {
