@@ -131,7 +131,8 @@ __device__ inline float4 pair_params(const StepView &sv, const int32_t *rows, in
 }
 
 // Second phase of the LDS epilogue of a BM x BN tile whose sums sit in C
-// (pitch CP floats; NH = 2: two k-half arrays BM * CP apart, added here).
+// (pitch CP floats; NH arrays of partial sums BM * CP apart, added here in
+// order).
 // Audio: each thread owns a fixed 4-column chunk and walks row pairs, adds the
 // bias, applies the CFG merge (Eq. 1) and 1/T, and stores 16 bytes per output
 // row.  Text: each thread scans whole 32-column parts of rows and writes the
@@ -143,13 +144,14 @@ __device__ __forceinline__ void epilogue_from_lds(const HeadView &hv, const Step
   const int tid = threadIdx.x;
   auto sum4 = [&](const float *p) __attribute__((always_inline)) {
     floatx4 v = *reinterpret_cast<const floatx4 *>(p);
-    if constexpr (NH == 2) v = v + *reinterpret_cast<const floatx4 *>(p + BM * CP);
+#pragma unroll
+    for (int h = 1; h < NH; ++h) v = v + *reinterpret_cast<const floatx4 *>(p + h * BM * CP);
     return v;
   };
   if constexpr (!TEXT) {
     constexpr int CH = BN / 4;
-    constexpr int ITEMS = (BM / 2) * CH / NT;
-    static_assert(ITEMS >= 1 && (BM / 2) * CH % NT == 0, "whole items per thread");
+    constexpr int TOTAL = (BM / 2) * CH, ITEMS = (TOTAL + NT - 1) / NT;
+    static_assert(NT % CH == 0, "a fixed column chunk per thread");
     const int c = tid % CH;
     const int nc = n0 + 4 * c;
     floatx4 bias = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -175,7 +177,7 @@ __device__ __forceinline__ void epilogue_from_lds(const HeadView &hv, const Step
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
       const int q = (it * NT + tid) / CH;
-      if (m0 + 2 * q >= M || nc >= N) continue;
+      if (q >= BM / 2 || m0 + 2 * q >= M || nc >= N) continue;
       const float *c0 = C + (2 * q) * CP + 4 * c;
       const floatx4 v0 = sum4(c0) + bias;
       const floatx4 v1 = sum4(c0 + CP) + bias;

@@ -140,3 +140,52 @@ def test_topk_infinite_scores_give_valid_ids(V, K, Rs, top_p):
     g = dw.tokens.cpu().numpy()[rows]
     assert np.all((g >= 0) & (g < V))
     assert g[0, 1] == 11 and g[1, 1] % 2 == 1
+
+
+# streaming tiles (copying and computing waves apart): 32, 64 and 128 rows by
+# 64, 128 (exactly 256 of them) and 256 columns, audio and text, at the edges
+# of their rows and columns; fewer slices of 64 k than ring stages, an odd
+# number of slices, and slice counts around the hidden rows' register buffers
+STREAM = [
+    # H, V, K, pairs, solo, text, V_text
+    (64, 33, 1, 16, 0, 1, 65),
+    (64, 4096, 8, 16, 1, 0, 0),
+    (192, 4096, 8, 32, 0, 0, 0),
+    (448, 4096, 8, 64, 0, 0, 0),
+    (576, 61, 3, 32, 1, 33, 129),
+    (832, 64, 2, 63, 2, 64, 63),
+    (128, 4096, 9, 15, 1, 32, 33001),
+    (960, 4096, 9, 1, 0, 0, 0),
+    (320, 4093, 9, 20, 24, 65, 32801),
+    (64, 300, 2, 64, 1, 128, 257),
+    (704, 1027, 3, 70, 13, 0, 0),
+]
+
+
+@pytest.mark.parametrize("H,V,K,pairs,solo,text,V_text", STREAM)
+def test_streaming_tile_edges(H, V, K, pairs, solo, text, V_text):
+    wl = inputs.Workload(f"stream_{H}_{V}", H=H, K=K, V=V, n_pairs=pairs, n_solo=solo, n_text=text,
+                         V_text=V_text, dtype="bf16", top_k=5, steps=2 * K, shuffle=True,
+                         bias=V % 2 == 1)
+    say(f"case {wl.name} R={wl.R} N={wl.N}")
+    check_one_step(wl, K, 1e-5)
+
+
+# audio rows beyond 128: whole rounds of 256 x 256 tiles against 128 x 256 ones
+# (the last round of the former full, half full and empty)
+ROWS = [
+    # V, K, pairs, solo
+    (4096, 8, 128, 0),
+    (4096, 8, 256, 0),
+    (4096, 8, 256, 1),
+    (4096, 6, 256, 256),
+    (3000, 5, 65, 30),
+]
+
+
+@pytest.mark.parametrize("V,K,pairs,solo", ROWS)
+def test_row_tile_choice(V, K, pairs, solo):
+    wl = inputs.Workload(f"rows_{V}_{K}_{pairs}", H=128, K=K, V=V, n_pairs=pairs, n_solo=solo,
+                         dtype="bf16", top_k=5, steps=2 * K, shuffle=True)
+    say(f"case {wl.name} R={wl.R} N={wl.N}")
+    check_one_step(wl, K, 1e-5)
