@@ -18,8 +18,8 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmcd.so")
 ARCH = "gfx950"
 
-SOURCES = ["mcd_api.cpp", "k_head_gemm.hip", "k_stream.hip", "k_mfma.hip", "k_fused.hip", "k_sample.hip",
-           "k_grid.hip", "k_embed.hip", "mcd_sched.cpp"]
+SOURCES = ["mcd_api.cpp", "k_head_gemm.hip", "k_stream.hip", "k_mfma.hip", "k_fused.hip",
+           "k_mixed_32.hip", "k_mixed_64.hip", "k_mixed_128.hip", "k_sample.hip", "k_grid.hip", "k_embed.hip", "mcd_sched.cpp"]
 
 COMMON = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra",

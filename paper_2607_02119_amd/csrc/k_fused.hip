@@ -38,11 +38,17 @@ hipError_t launch_mixed(const HeadView &hv, const StepView &sv, int n_audio, hip
 hipError_t launch_mixed_gemm(const HeadView &hv, const StepView &sv, hipStream_t st,
                              bool *launched) {
   *launched = false;
-  // audio rows in 256 x 256 tiles (at least one full round of them), text rows
-  // in one row tile of 65..128 rows
-  if (hv.dtype != MCD_BF16 || sv.Mg <= 128 || sv.n_text <= 64 || sv.n_text > 128) return hipSuccess;
+  if (hv.dtype != MCD_BF16 || sv.Mg < 1 || sv.n_text < 1 || sv.n_text > 128) return hipSuccess;
+  // audio rows in 256 x 256 tiles (at least one full round of them) and text
+  // rows in one row tile of 65..128 rows; streaming tiles for both otherwise
   const int64_t n_audio = tiles_256(sv.Mg, hv.N);
-  if (n_audio < 256 || n_audio > (1 << 20)) return hipSuccess;
+  if (sv.Mg <= 128 || sv.n_text <= 64 || n_audio < 256) {
+    if (n_audio > (1 << 18)) return hipSuccess;
+    *launched = true;
+    if (sv.n_text <= 32) return launch_mixed_text_32(hv, sv, st);
+    return sv.n_text <= 64 ? launch_mixed_text_64(hv, sv, st) : launch_mixed_text_128(hv, sv, st);
+  }
+  if (n_audio > (1 << 20)) return hipSuccess;
   *launched = true;
   // the text tile width of the streaming launch for the same rows
   const int t128 = (hv.V_text + 127) / 128;

@@ -33,13 +33,12 @@ hipError_t launch_rows(const HeadView &hv, const StepView &sv, int M, int N, hip
   const int t128 = (N + 127) / 128;
   if (t128 < 256) return launch_pc<BM, 64, TEXT>(hv, sv, M, N, st);
   if (t128 == 256) return launch_pc<BM, 128, TEXT>(hv, sv, M, N, st);
-  return launch_pc<BM, 256, TEXT>(hv, sv, M, N, st);
+  return launch_pc<BM, wide_columns(BM), TEXT>(hv, sv, M, N, st);
 }
 
 // Weight-streaming launch for M <= 128 rows: 64-column tiles when 128-column
 // ones would leave compute units idle, 128-column tiles when they make exactly
-// one round, and 256-column tiles (half the hidden-state bytes per weight
-// byte) when there is more than one round.
+// one round, and wide ones when there is more than one round.
 template <bool TEXT>
 hipError_t launch_skinny(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
   if (M <= 32) return launch_rows<32, TEXT>(hv, sv, M, N, st);

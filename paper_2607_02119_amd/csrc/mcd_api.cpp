@@ -368,8 +368,8 @@ size_t mcd_workspace_bytes(const mcd_head *h, int32_t R) {
 
 namespace {
 
-// K1 for one batch.  Audio and text rows together: one launch of both when
-// the batch has that shape, else the audio projection on the caller's stream
+// K1 for one batch.  Audio and text rows together: one launch of both up to
+// 128 text rows, else the audio projection on the caller's stream
 // and the text projection on the head's second stream, both after everything
 // already on the caller's stream, which waits for both.
 hipError_t run_head_gemm(const mcd_head *h, const mcd::StepView &sv, hipStream_t stream) {

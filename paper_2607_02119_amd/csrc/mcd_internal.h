@@ -82,11 +82,14 @@ hipError_t launch_stream_gemm(const HeadView &hv, const StepView &sv, bool text,
                               hipStream_t stream);   // at most 128 GEMM rows
 hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text,
                             hipStream_t stream);     // any number of rows
-// A batch of audio rows in 256 x 256 tiles and 65..128 text rows: both
-// projections in one launch; *launched is false (and nothing is launched) for
-// other batches.
+// A batch of audio rows and at most 128 text rows: both projections in one
+// launch; *launched is false (and nothing is launched) for other batches.
 hipError_t launch_mixed_gemm(const HeadView &hv, const StepView &sv, hipStream_t st,
                              bool *launched);
+// its streaming tiles, by text rows (one file each: many tile shapes)
+hipError_t launch_mixed_text_32(const HeadView &hv, const StepView &sv, hipStream_t st);
+hipError_t launch_mixed_text_64(const HeadView &hv, const StepView &sv, hipStream_t st);
+hipError_t launch_mixed_text_128(const HeadView &hv, const StepView &sv, hipStream_t st);
 // Next-step input (k_embed.hip): sizes and pointers validated by the caller.
 struct EmbedView {
   int32_t R, H, K, V, pad_id, V_text;

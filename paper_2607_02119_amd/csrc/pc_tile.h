@@ -37,8 +37,11 @@ struct PcShape {
   static constexpr int MB = BM / 32, NB = WN / 32;
   static constexpr int WST = BN * ROWB, AST = BM * ROWB;
   static constexpr int WIW = WST / 1024 / 2, AIA = AST / 1024 / 2;   // copies per wave and slice
-  // 32 rows: half of the LDS, so that two tiles share a compute unit
-  static constexpr int kBudget = (BM == 32 && BN == 64 ? 80 : 160) * 1024;
+  // 32 rows: half of the LDS, so that two tiles share a compute unit and the
+  // start and end of one run under the other's loop (24 text rows, 151936 x
+  // 4096: 207 us at one tile per compute unit, 200 at two, 210 with 256
+  // columns; 6.2 TB/s)
+  static constexpr int kBudget = (BM == 32 && BN <= 128 ? 80 : 160) * 1024;
   static constexpr int SA = BN == 64 ? 3 : 2;
   static constexpr int HL = BM == 128 ? 6 : 8;   // hidden slices in flight in registers
   static constexpr int SW0 = (kBudget - SA * AST) / WST, SWV = 63 / WIW + 1;   // counter range
@@ -50,6 +53,11 @@ struct PcShape {
   static constexpr int kLds = kRing > kEpi ? kRing : kEpi;
   static_assert(SW >= 3 && (SW - 1) * WIW < 64 && kLds <= 160 * 1024, "ring depths");
 };
+
+// Columns of a tile when 128-column tiles make more than one round: 256, half
+// the hidden-state bytes per weight byte, or 128 for 32 rows, whose hidden
+// states are few.
+constexpr int wide_columns(int bm) { return bm == 32 ? 128 : 256; }
 
 // One BM x BN tile (tile index bx: row tile bx % tiles_m, column tile
 // bx / tiles_m) with 512 threads and the workgroup's LDS buffer `lds` of

@@ -15,6 +15,8 @@ if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
 from paper_2607_02119_amd import harness  # noqa: E402
+from tests.test_gpu_graph import (  # noqa: E402
+    test_step_replayed_from_a_graph_equals_eager as replay)
 
 GAP_TOL, TOPK_TOL, TOPP_TOL = 1e-3, 1e-4, 1e-5
 
@@ -189,3 +191,37 @@ def test_row_tile_choice(V, K, pairs, solo):
                          dtype="bf16", top_k=5, steps=2 * K, shuffle=True)
     say(f"case {wl.name} R={wl.R} N={wl.N}")
     check_one_step(wl, K, 1e-5)
+
+
+# audio and text rows in one launch of streaming tiles: every pair of row
+# heights (audio rows beyond 128 too), narrow and wide columns on either side
+MIXED = [
+    # V, K, pairs, solo, text, V_text
+    (50, 2, 1, 0, 1, 33),
+    (60, 3, 16, 0, 33, 200),
+    (61, 3, 15, 1, 65, 32801),
+    (70, 3, 16, 1, 32, 32801),
+    (300, 2, 32, 0, 64, 100),
+    (4096, 9, 20, 2, 128, 70),
+    (33, 2, 32, 1, 20, 150),
+    (4093, 9, 64, 0, 40, 32900),
+    (90, 4, 60, 8, 100, 64),
+    (100, 3, 64, 1, 9, 32801),
+    (1000, 4, 80, 9, 60, 90),
+    (700, 3, 130, 0, 128, 300),
+]
+
+
+@pytest.mark.parametrize("V,K,pairs,solo,text,V_text", MIXED)
+def test_mixed_streaming_launch(V, K, pairs, solo, text, V_text):
+    wl = inputs.Workload(f"mixed_{V}_{text}", H=192, K=K, V=V, n_pairs=pairs, n_solo=solo,
+                         n_text=text, V_text=V_text, dtype="bf16", top_k=5, steps=2 * K,
+                         shuffle=True, bias=V % 2 == 1)
+    say(f"case {wl.name} R={wl.R} N={wl.N}")
+    check_one_step(wl, K, 1e-5)
+
+
+def test_two_stream_step_replayed_from_a_graph():
+    """More than 128 text rows: audio and text rows on two streams, fork and join in the graph."""
+    replay("two_streams", dict(H=128, K=3, V=37, n_pairs=10, n_solo=5, n_text=150, V_text=300,
+                               dtype="bf16", top_k=7, steps=6, shuffle=True))
