@@ -14,7 +14,7 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_2607_02119_amd import harness  # noqa: E402
+from paper_2607_02119_amd import harness, mcd  # noqa: E402
 from tests.test_gpu_graph import (  # noqa: E402
     test_step_replayed_from_a_graph_equals_eager as replay)
 
@@ -225,3 +225,43 @@ def test_two_stream_step_replayed_from_a_graph():
     """More than 128 text rows: audio and text rows on two streams, fork and join in the graph."""
     replay("two_streams", dict(H=128, K=3, V=37, n_pairs=10, n_solo=5, n_text=150, V_text=300,
                                dtype="bf16", top_k=7, steps=6, shuffle=True))
+
+
+# delay pattern: one thread per token below 64 frames (steps), one per frame
+# (step) from there; codebook counts around the eight in flight and the
+# 16-byte store; large and equal delays, F = 0
+DELAY = [
+    # n_req, K, F, delays
+    (3, 8, 64, range(8)),
+    (2, 8, 63, range(8)),
+    (5, 7, 200, (0, 3, 3, 1, 0, 9, 2)),
+    (2, 9, 65, range(9)),
+    (1, 32, 130, range(31, -1, -1)),
+    (4, 12, 257, [100] * 12),
+    (600, 4, 300, (0, 1, 2, 3)),
+    (3, 1, 64, (5,)),
+    (2, 4, 0, (0, 1, 2, 70)),
+]
+
+
+@pytest.mark.parametrize("n_req,K,F,delays", DELAY)
+@pytest.mark.parametrize("shift", [0, 1])
+def test_delay_pattern_rows(n_req, K, F, delays, shift):
+    """`shift`: the stream buffer starts that many tokens past a 16-byte boundary."""
+    delays = np.array(list(delays), np.int32)
+    say(f"case delay n_req={n_req} K={K} F={F} shift={shift}")
+    T = F + int(delays.max())
+    G = np.random.default_rng(K).integers(0, 4096, (n_req, K, F)).astype(np.int32)
+    buf = torch.full((n_req * T * K + shift,), -7, dtype=torch.int32, device="cuda")
+    streams = buf[shift:].view(n_req, T, K)
+    grid = torch.from_numpy(G).cuda()
+    mcd.mcd_interleave(grid, delays, 4096, streams)
+    back = torch.full_like(grid, -7)
+    mcd.mcd_deinterleave(streams, delays, back)
+    torch.cuda.synchronize()
+    want = np.full((n_req, T, K), 4096, np.int32)
+    for k, dk in enumerate(delays):
+        want[:, dk:dk + F, k] = G[:, k]
+    assert np.array_equal(streams.cpu().numpy(), want)
+    assert np.array_equal(back.cpu().numpy(), G)
+    assert (buf[:shift] == -7).all()
