@@ -142,18 +142,23 @@ def _check(code, where):
 
 def _ptr(t):
     """Device (or host numpy) pointer of an optional tensor / array."""
-    if t is None:
-        return None
     if isinstance(t, torch.Tensor):
         return t.data_ptr()
+    if t is None:
+        return None
     if isinstance(t, np.ndarray):
         return t.ctypes.data
     return int(t)
 
 
+# torch.cuda.current_stream() builds a Stream object on every call (2.9 us); the
+# raw handle of the same stream takes 0.2 us.
+_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+
+
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return _raw_stream(_device())
     return stream.cuda_stream if isinstance(stream, torch.cuda.Stream) else int(stream)
 
 
