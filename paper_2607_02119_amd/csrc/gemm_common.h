@@ -150,8 +150,8 @@ __device__ __forceinline__ void epilogue_from_lds(const HeadView &hv, const Step
   };
   if constexpr (!TEXT) {
     constexpr int CH = BN / 4;
-    constexpr int TOTAL = (BM / 2) * CH, ITEMS = (TOTAL + NT - 1) / NT;
-    static_assert(NT % CH == 0, "a fixed column chunk per thread");
+    // threads at work: whole rows of chunks, so that a thread keeps its chunk
+    constexpr int NA = NT / CH * CH, TOTAL = (BM / 2) * CH, ITEMS = (TOTAL + NA - 1) / NA;
     const int c = tid % CH;
     const int nc = n0 + 4 * c;
     floatx4 bias = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -176,8 +176,8 @@ __device__ __forceinline__ void epilogue_from_lds(const HeadView &hv, const Step
     };
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
-      const int q = (it * NT + tid) / CH;
-      if (q >= BM / 2 || m0 + 2 * q >= M || nc >= N) continue;
+      const int q = (it * NA + tid) / CH;
+      if (tid >= NA || q >= BM / 2 || m0 + 2 * q >= M || nc >= N) continue;
       const float *c0 = C + (2 * q) * CP + 4 * c;
       const floatx4 v0 = sum4(c0) + bias;
       const floatx4 v1 = sum4(c0 + CP) + bias;

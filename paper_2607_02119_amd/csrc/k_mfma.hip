@@ -284,15 +284,14 @@ hipError_t launch_mfma(const HeadView &hv, const StepView &sv, int M, int N, hip
 
 hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text, hipStream_t st) {
   if (text) return launch_mfma<true>(hv, sv, sv.n_text, hv.V_text, st);
-  // 256 x 256 tiles or the streaming path's 128 x 256 tiles, whichever needs
-  // less time in whole rounds of 256 compute units.  A round of the former
-  // takes about twice one of the latter, a little less (H 4096: 132 against
-  // 139 us at one and two rounds, 541 against 600 at four and eight), so they
-  // win unless their last round is at most half full (384 tiles in two rounds
-  // 257 us, 768 in three 235; 128 tiles in one round 132, 256 in one 70).
-  const int64_t wide = (tiles_256(sv.Mg, hv.N) + 255) / 256;
-  const int64_t rows = ((int64_t)((sv.Mg + 127) / 128) * ((hv.N + 255) / 256) + 255) / 256;
-  if (rows < 2 * wide) return launch_stream_rows(hv, sv, st);
+  // 256 x 256 tiles or the streaming path's, whichever needs less time.  A
+  // round of 256 of the former takes about 730 in the unit of stream_cost (H
+  // 4096: 132 us, against 139 for two rounds of 128 x 256 streaming tiles, 2 x
+  // 384; 541 against 600 for four and eight), so they win where their last
+  // round is more than half full (384 tiles in two rounds 257 us, 768
+  // streaming tiles in three 235).
+  const int64_t wide = (tiles_256(sv.Mg, hv.N) + 255) / 256 * 730;
+  if (stream_cost(sv.Mg, hv.N) < wide) return launch_stream_gemm(hv, sv, false, st);
   return launch_mfma2(hv, sv, st);
 }
 

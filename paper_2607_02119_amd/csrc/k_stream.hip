@@ -1,6 +1,6 @@
-// K1, weight-streaming path (at most 128 GEMM rows; also audio batches of
-// more than 128 rows whose rounds 256 x 256 tiles do not fill, in 128-row
-// tiles): codebook-head projection
+// K1, weight-streaming path (text batches of at most 128 rows, and audio
+// batches of any number of rows where 256 x 256 tiles would take longer):
+// codebook-head projection
 // with the CFG merge and temperature fused into the epilogue, or the text-head
 // projection with a fused (max, lowest argmax) epilogue.
 //
@@ -28,38 +28,65 @@ hipError_t launch_pc(const HeadView &hv, const StepView &sv, int M, int N, hipSt
   return hipGetLastError();
 }
 
-template <int BM, bool TEXT>
-hipError_t launch_rows(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
-  const int t128 = (N + 127) / 128;
-  if (t128 < 256) return launch_pc<BM, 64, TEXT>(hv, sv, M, N, st);
-  if (t128 == 256) return launch_pc<BM, 128, TEXT>(hv, sv, M, N, st);
-  return launch_pc<BM, wide_columns(BM), TEXT>(hv, sv, M, N, st);
+// Up to 32 rows the hidden states are few and the weights' HBM reads bound the
+// tile: 64-column tiles when 128-column ones would leave compute units idle,
+// else 128-column ones.
+template <bool TEXT>
+hipError_t launch_few_rows(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
+  if ((N + 127) / 128 < 256) return launch_pc<32, 64, TEXT>(hv, sv, M, N, st);
+  return launch_pc<32, wide_columns(32), TEXT>(hv, sv, M, N, st);
 }
 
-// Weight-streaming launch for M <= 128 rows: 64-column tiles when 128-column
-// ones would leave compute units idle, 128-column tiles when they make exactly
-// one round, and wide ones when there is more than one round.
+// More rows: a tile takes in (BM + BN) x H x 2 bytes, and that rate bounds it,
+// so a launch takes about rounds of 256 compute units x (BM + BN).  The shape
+// with the least of that; the larger of equals (fewer re-reads).  Measured (H
+// 4096, us, 32 x 64 / 64 x 64 / 64 x 96 / 128 x 64 tiles, the choice marked):
+// 128 rows of 2048 columns 18.0* / 21.6 / 27.1 / 29.1; of 8192 32.7 / 26.7* /
+// 29.0 / 32.1; of 12288 44.8 / 44.8 / 29.5* / 33.7; of 16384 61.5 / 49.9 / 56.0
+// / 38.8*; of 32768 54 with 128 x 128; 512 rows of 16384 70 with 128 x 256.
+struct TileShape {
+  int bm, bn;
+};
+constexpr TileShape kShapes[] = {{128, 256}, {128, 128}, {128, 64}, {64, 256},
+                                 {64, 128},  {64, 96},   {64, 64},  {32, 64}};
+
+int64_t cost_of(const TileShape &t, int M, int N) {
+  const int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  return (tiles + 255) / 256 * (t.bm + t.bn);
+}
+
+int best_shape(int M, int N) {
+  int best = -1;
+  for (int i = 0; i < (int)(sizeof kShapes / sizeof kShapes[0]); ++i) {
+    if (M <= 64 && kShapes[i].bm > 64) continue;   // rows of padding
+    if (best < 0 || cost_of(kShapes[i], M, N) < cost_of(kShapes[best], M, N)) best = i;
+  }
+  return best;
+}
+
 template <bool TEXT>
-hipError_t launch_skinny(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
-  if (M <= 32) return launch_rows<32, TEXT>(hv, sv, M, N, st);
-  if (M <= 64) return launch_rows<64, TEXT>(hv, sv, M, N, st);
-  return launch_rows<128, TEXT>(hv, sv, M, N, st);
+hipError_t launch_tiles(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
+  if (M <= 32) return launch_few_rows<TEXT>(hv, sv, M, N, st);
+  switch (best_shape(M, N)) {
+    case 0: return launch_pc<128, 256, TEXT>(hv, sv, M, N, st);
+    case 1: return launch_pc<128, 128, TEXT>(hv, sv, M, N, st);
+    case 2: return launch_pc<128, 64, TEXT>(hv, sv, M, N, st);
+    case 3: return launch_pc<64, 256, TEXT>(hv, sv, M, N, st);
+    case 4: return launch_pc<64, 128, TEXT>(hv, sv, M, N, st);
+    case 5: return launch_pc<64, 96, TEXT>(hv, sv, M, N, st);
+    case 6: return launch_pc<64, 64, TEXT>(hv, sv, M, N, st);
+    default: return launch_pc<32, 64, TEXT>(hv, sv, M, N, st);
+  }
 }
 
 }  // namespace
 
-// Audio batches of more than 128 GEMM rows (the cfg workloads' 512 rows) in
-// 128 x 256 tiles, row tile by row tile: 256 pairs or 512 solo rows of 16 x
-// 1024 ids take 66-70 us, 72-83 with copying and computing in the same four
-// waves.
-hipError_t launch_stream_rows(const HeadView &hv, const StepView &sv, hipStream_t st) {
-  return launch_pc<128, 256, false>(hv, sv, sv.Mg, hv.N, st);
-}
+int64_t stream_cost(int32_t M, int32_t N) { return cost_of(kShapes[best_shape(M, N)], M, N); }
 
 hipError_t launch_stream_gemm(const HeadView &hv, const StepView &sv, bool text,
                               hipStream_t st) {
-  return text ? launch_skinny<true>(hv, sv, sv.n_text, hv.V_text, st)
-              : launch_skinny<false>(hv, sv, sv.Mg, hv.N, st);
+  return text ? launch_tiles<true>(hv, sv, sv.n_text, hv.V_text, st)
+              : launch_tiles<false>(hv, sv, sv.Mg, hv.N, st);
 }
 
 }  // namespace mcd

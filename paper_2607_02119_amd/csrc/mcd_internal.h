@@ -76,10 +76,11 @@ hipError_t launch_head_gemm(const HeadView &hv, const StepView &sv, hipStream_t 
 hipError_t launch_head_gemm_part(const HeadView &hv, const StepView &sv, bool text,
                                  hipStream_t stream);
 // bf16 projection kernels (audio rows, or the text rows when text is set)
-hipError_t launch_stream_rows(const HeadView &hv, const StepView &sv,
-                              hipStream_t st);       // audio rows in 128 x 256 tiles
+// streaming tiles, any number of rows; stream_cost: their time for M rows of N
+// columns, in rounds of 256 tiles x (tile rows + tile columns)
 hipError_t launch_stream_gemm(const HeadView &hv, const StepView &sv, bool text,
-                              hipStream_t stream);   // at most 128 GEMM rows
+                              hipStream_t stream);
+int64_t stream_cost(int32_t M, int32_t N);
 hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text,
                             hipStream_t stream);     // any number of rows
 // A batch of audio rows and at most 128 text rows: both projections in one

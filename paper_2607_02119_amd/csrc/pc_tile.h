@@ -77,12 +77,13 @@ __device__ __forceinline__ void pc_tile(const HeadView &hv, const StepView &sv, 
   const int NST = H / SK;
   const int tiles_m = (M + BM - 1) / BM;
   // Several row tiles: workgroups are dealt to the 8 XCDs in turn, so the
-  // index is remapped to give each XCD a contiguous run of tiles, in which the
-  // row tiles of a column tile are neighbours, run at the same time and walk k
-  // in the same order: they share that column tile's weights through the L2.
+  // index is remapped to give each XCD a contiguous run of tiles (one more in
+  // the first XCDs where the runs are not equal), in which the row tiles of a
+  // column tile are neighbours, run at the same time and walk k in the same
+  // order: they share that column tile's weights through the L2.
   if (tiles_m > 1) {
     const int ntiles = tiles_m * ((N + BN - 1) / BN);
-    if (ntiles % 8 == 0) bx = (bx % 8) * (ntiles / 8) + bx / 8;
+    bx = (bx % 8) * (ntiles / 8) + min(bx % 8, ntiles % 8) + bx / 8;
   }
   const int tile_m = bx % tiles_m, tile_n = bx / tiles_m;
   const int m0 = tile_m * BM, n0 = tile_n * BN;

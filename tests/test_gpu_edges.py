@@ -265,3 +265,30 @@ def test_delay_pattern_rows(n_req, K, F, delays, shift):
     assert np.array_equal(streams.cpu().numpy(), want)
     assert np.array_equal(back.cpu().numpy(), G)
     assert (buf[:shift] == -7).all()
+
+
+# the tile shape chosen by rounds x (rows + columns), each shape with ragged
+# rows and columns and with several row tiles (runs per XCD of unequal length)
+SHAPES = [
+    # V, K, pairs, solo, text, V_text         audio tile (text tile)
+    (1003, 7, 37, 21, 0, 0),                # 64 x 64, two row tiles
+    (4095, 3, 64, 0, 0, 0),                 # 64 x 96, two row tiles
+    (4001, 6, 20, 0, 0, 0),                 # 64 x 96
+    (4096, 2, 100, 0, 0, 0),                # 128 x 64, two row tiles
+    (4093, 2, 140, 20, 0, 0),               # 128 x 128, three row tiles
+    (4003, 5, 40, 20, 0, 0),                # 128 x 128
+    (2001, 1, 65, 0, 0, 0),                 # 32 x 64, five row tiles
+    (257, 1, 250, 3, 0, 0),                 # 32 x 64, sixteen row tiles
+    (10, 1, 0, 0, 95, 7021),                # text alone: 64 x 64
+    (10, 1, 0, 0, 120, 12290),              # 64 x 96
+    (10, 1, 0, 0, 40, 2000),                # 32 x 64, two row tiles
+]
+
+
+@pytest.mark.parametrize("V,K,pairs,solo,text,V_text", SHAPES)
+def test_tile_shapes(V, K, pairs, solo, text, V_text):
+    wl = inputs.Workload(f"shape_{V}_{K}_{pairs}_{text}", H=128, K=K, V=V, n_pairs=pairs,
+                         n_solo=solo, n_text=text, V_text=V_text, dtype="bf16", top_k=5,
+                         steps=2 * K + 1, shuffle=True)
+    say(f"case {wl.name} R={wl.R} N={wl.N}")
+    check_one_step(wl, K, 1e-5)
