@@ -23,12 +23,12 @@
 //
 // Selection.  A top-k cut usually goes through a short list of the ids above a
 // bound near the k-th score (topk_by_list), which one wave finishes.  Vectors
-// that it does not serve go through bins.  Every score s falls in a bin b = floor(16 (max - s)) (bins of
-// width 1/16 below the maximum, the last one open-ended); the bin index is
-// monotone in s, so a cut between bins is a cut in the (score desc, id asc)
-// order.  One histogram pass (counts for top-k, masses for top-p) finds the bin
-// holding the cut; only the few elements of that bin are then ranked exactly
-// against each other.  Top-p masses are fixed-point exp(s - max) * 2^48 (fp32
+// that it does not serve go through bins.  Every score s falls in a bin
+// b = floor(16 (max - s)) (bins of width 1/16 below the maximum, the last one
+// open-ended); the bin index is monotone in s, so a cut between bins is a cut in
+// the (score desc, id asc) order.  One histogram pass (counts for top-k, masses
+// for top-p) finds the bin holding the cut; only the few elements of that bin
+// are then ranked exactly against each other.  Top-p masses are fixed-point exp(s - max) * 2^48 (fp32
 // exp, converted exactly) summed as 64-bit integers: exact and independent of
 // the order of the adds.  Inputs whose cut bin is crowded (heavy ties, or a cut
 // far below the maximum) take a radix select over order-preserving 32-bit keys

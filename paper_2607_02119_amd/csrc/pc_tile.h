@@ -1,5 +1,7 @@
-// Tile body of the K1 weight-streaming path with copying and computing waves
-// apart: the same projection and epilogues as stream_tile.h.
+// Tile body of the K1 weight-streaming path, copying and computing waves apart:
+// codebook-head projection with the CFG merge and temperature fused into the
+// epilogue (TEXT = false), or the text-head projection with a fused (max, lowest
+// argmax) epilogue; the formulas are at the head of k_stream.hip.
 #pragma once
 
 #include "stream_tile.h"

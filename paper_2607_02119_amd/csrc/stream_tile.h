@@ -1,13 +1,12 @@
-// Tile body of the K1 weight-streaming path (at most 128 GEMM rows per tile):
-// codebook-head projection with the CFG merge and temperature fused into the
-// epilogue, or the text-head projection with a fused (max, lowest argmax)
-// epilogue.
+// Streaming tile of the mixed launch's text rows (at most 128, beside 256 x 256
+// audio tiles): the text-head projection with a fused (max, lowest argmax)
+// epilogue,
 //
-//   logits[g][n] = sum_h hidden[row(g)][h] * W[n][h]         (Sec. 2.1, n = k*V + v)
-//   pair p (GEMM rows 2p, 2p+1 = Main, Companion):
-//     scores[p][n] = (w * l_main + (1 - w) * l_comp) / T    (Eq. 1, Sec. 2.4)
-//   solo row j:  scores[n_pairs + j][n] = l / T;  T = 0 (greedy): no division
-//   text rows:   per row and 32-column part, the largest logit and its lowest id.
+//   logits[g][n] = sum_h hidden[row(g)][h] * W_text[n][h]
+//   per row and 32-column part, the largest logit and its lowest id.
+//
+// The streaming launches proper take the eight-wave tile of pc_tile.h, which
+// shares the LDS layout and the waits defined here.
 #pragma once
 
 #include "gemm_common.h"
@@ -15,15 +14,15 @@
 namespace mcd {
 namespace {
 
-// Weight-streaming path, tiles of up to 128 rows.  A workgroup owns BM rows
-// (all of them when there are at most 128) and BN columns.  Each k slice of SK = 64 (128 bytes of every weight and hidden
-// row) goes into one of the LDS stages of its ring.  Waves 0-1 copy weight
-// slices with global_load_lds_dwordx4 (64 lanes x 16 B, eight 128-byte row
-// segments per instruction, no registers), SW - 1 slices ahead of their use.
-// Waves 2-3 load hidden-state slices into registers HL slices ahead and write
-// them to a two-stage ring one slice ahead.  Waves split the tile 2 x 2
-// (column half w % 2, k32 half w / 2 of every slice; the two k halves meet in
-// LDS at the end) or, for 256-column tiles, 4 x 1 (column quarter, all of k).
+// A workgroup of four waves owns all rows (at most BM) and BN columns.  Each k
+// slice of SK = 64 (128 bytes of every weight and hidden row) goes into one of
+// the LDS stages of its ring.  Waves 0-1 copy weight slices with
+// global_load_lds_dwordx4 (64 lanes x 16 B, eight 128-byte row segments per
+// instruction, no registers), SW - 1 slices ahead of their use.  Waves 2-3 load
+// hidden-state slices into registers HL slices ahead and write them to a
+// two-stage ring one slice ahead.  Waves split the tile 2 x 2 (column half
+// w % 2, k32 half w / 2 of every slice; the two k halves meet in LDS at the
+// end) or, for 256-column tiles, 4 x 1 (column quarter, all of k).
 //
 // Every byte a compute unit takes in, from HBM or from L2, crosses the L2 ->
 // CU path, and that path (about 45-50 GB/s per CU measured) bounds the loop:
@@ -87,49 +86,30 @@ struct DmaShape {
   static_assert((SW - 2) * WIW < 64 && HL * AIA < 64, "vmcnt range");
 };
 
-// One BM x BN tile (tile index bx: row tile bx % tiles_m, column tile
-// bx / tiles_m) with 256 threads and the workgroup's LDS buffer `lds` of
+// One BM x BN tile (column tile bx) with 256 threads and the workgroup's LDS buffer `lds` of
 // DmaShape<BM, BN>::kLds bytes (1024-byte aligned).
-template <int BM, int BN, bool TEXT>
+template <int BM, int BN>
 __device__ __forceinline__ void dma_tile(const HeadView &hv, const StepView &sv, int bx,
                                          char *lds) {
   using S_ = DmaShape<BM, BN>;
   constexpr int SK = S_::SK, MB = S_::MB, KSPLIT = S_::KSPLIT, CSPLIT = S_::CSPLIT, KS = S_::KS;
   constexpr int WN = S_::WN, NB = S_::NB, ROWB = S_::ROWB, WST = S_::WST, AST = S_::AST;
   constexpr int SA = S_::SA, HL = S_::HL, SW = S_::SW, WIW = S_::WIW, AIA = S_::AIA;
-  constexpr int LDSB = S_::kLds;
   char *const wring = lds;                 // weight stages
   char *const aring = lds + SW * WST;      // hidden-state stages
   // Epilogue, after the loop (the rings are free then): the partial sums C of
-  // the two k halves at the start, and per pair of GEMM rows (2q, 2q + 1)
-  // {w, 1/T, out, -2} for a CFG pair or {1/T_0, 1/T_1, out_0, out_1} for two solo
-  // rows (out -1: no row) at the end.
+  // the two k halves.
   constexpr int CP = BN + 4;               // padded row pitch of C (floats)
-  constexpr int RPOFF = LDSB - (BM / 2) * 16;
-  static_assert(KSPLIT * BM * CP * 4 <= RPOFF, "C and the row parameters fit the rings");
-  float4 *const rowp = reinterpret_cast<float4 *>(lds + RPOFF);
+  static_assert(KSPLIT * BM * CP * 4 <= S_::kLds, "C fits the rings");
 
-  const int32_t *rows = sv.plan + kPlanHeader + (TEXT ? sv.Mg : 0);
-  const int M = TEXT ? sv.n_text : sv.Mg;
-  const int N = TEXT ? hv.V_text : hv.N;
-  const __bf16 *Wp = static_cast<const __bf16 *>(TEXT ? hv.W_text : hv.W);
+  const int32_t *rows = sv.plan + kPlanHeader + sv.Mg;
+  const int M = sv.n_text, N = hv.V_text;
+  const __bf16 *Wp = static_cast<const __bf16 *>(hv.W_text);
   const __bf16 *X = static_cast<const __bf16 *>(sv.hidden);
   const int H = hv.H;
   const int NST = H / SK;
 
-  const int tiles_m = (M + BM - 1) / BM;
-  // Several row tiles (more than 128 audio rows): workgroups are dealt to the
-  // 8 XCDs in turn, so the index is remapped to give each XCD a contiguous
-  // run of tiles, in which the row tiles of a column tile are neighbours, run
-  // at the same time and walk k in the same order: they share that column
-  // tile's weights through the XCD's L2.
-  if (tiles_m > 1) {
-    const int ntiles = tiles_m * ((N + BN - 1) / BN);
-    if (ntiles % 8 == 0) bx = (bx % 8) * (ntiles / 8) + bx / 8;
-  }
-  const int tile_m = bx % tiles_m;
-  const int tile_n = bx / tiles_m;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int n0 = bx * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ch = wave % CSPLIT, kh = wave / CSPLIT;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
@@ -139,7 +119,7 @@ __device__ __forceinline__ void dma_tile(const HeadView &hv, const StepView &sv,
   // moment the workgroups read different offsets of their (8 KiB-strided)
   // weight rows and spread over the HBM channels instead of all hitting the
   // same ones.  The sum order per tile is fixed, so results stay deterministic.
-  const int kskew = (int)(((unsigned)tile_n * 7u) % (unsigned)NST);
+  const int kskew = (int)(((unsigned)bx * 7u) % (unsigned)NST);
   const uint32_t wbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)wring;
   const int seg_r = lane >> 3, seg_c = lane & 7;
 
@@ -209,26 +189,15 @@ __device__ __forceinline__ void dma_tile(const HeadView &hv, const StepView &sv,
   }
 
   // The hidden-state waves gather their rows through the plan and start their
-  // copies as soon as the row indices are in.  The per-row epilogue parameters
-  // are loaded before the copies (in order, they complete before them, so the
-  // loop's copy counts stay valid) and staged in LDS after the loop.
-  const int q2 = tid - 128;
-  PairLoads praw{0.0f, 0.0f, 0.0f, 0, false, false};
+  // copies as soon as the row indices are in.
   if (!w_copier) {
-    // all row loads first (the copy sources and, for the epilogue, the rows of
-    // a GEMM row pair per thread), then the checks: their round trips overlap
+    // all row loads first, then the checks: their round trips overlap
     int prow[QN];
     static_for<0, QN>([&](auto qc) __attribute__((always_inline)) {
       constexpr int q = decltype(qc)::value;
       prow[q] = 0;
-      if (q < AIA) prow[q] = rows[min(m0 + ((wave_s - 2) * AIA + q) * 8 + seg_r, M - 1)];
+      if (q < AIA) prow[q] = rows[min(((wave_s - 2) * AIA + q) * 8 + seg_r, M - 1)];
     });
-    const int g0 = m0 + 2 * min(q2, BM / 2 - 1);
-    int pr0 = 0, pr1 = 0;
-    if constexpr (!TEXT) {
-      pr0 = rows[min(g0, sv.Mg - 1)];
-      pr1 = rows[min(g0 + 1, sv.Mg - 1)];
-    }
     bool bad = false;
     static_for<0, QN>([&](auto qc) __attribute__((always_inline)) {
       constexpr int q = decltype(qc)::value;
@@ -240,7 +209,6 @@ __device__ __forceinline__ void dma_tile(const HeadView &hv, const StepView &sv,
         src[q] = X + (size_t)(ok ? prow[q] : 0) * H + ((seg_c ^ ((r >> 1) & 7)) * 8);
       }
     });
-    if constexpr (!TEXT) praw = pair_params_load(sv, g0, pr0, pr1);
     if (bad) atomicOr(sv.status, (uint32_t)MCD_DEV_BAD_PLAN);
     // slices 0 .. SA - 2 straight into their stages, then HL slices ahead
     u32x4 h0[SA - 1][AIA];
@@ -397,14 +365,11 @@ __device__ __forceinline__ void dma_tile(const HeadView &hv, const StepView &sv,
   // all of them, and this drain makes that explicit before LDS is reused
   wait_vmem_and_lds<0>();
   __syncthreads();
-  if (!TEXT && !w_copier && q2 < BM / 2) rowp[q2] = pair_params_finish(sv, praw);
 
   // Epilogue, in two phases through LDS (the rings are free now).
   // Phase 1: every wave writes its partial sums (its k group) to C[kh][row][col].
-  // Phase 2: each thread takes 16-byte column chunks (audio) or 32-column text
-  // parts of whole rows, adds the k groups' sums (at most two terms: order-
-  // free), and applies the fused epilogue with coalesced stores.  No global
-  // load is left pending among the stores, so they never wait for each other.
+  // Phase 2: each thread takes 32-column text parts of whole rows, adds the k
+  // groups' sums (at most two terms: order-free) and writes their maxima.
   float *C = reinterpret_cast<float *>(lds);
   float *Cl = C + (kh * BM + (lane >> 5) * 4) * CP + ch * WN + frow;
   static_for<0, MB * NB * 16>([&](auto fc) __attribute__((always_inline)) {
@@ -414,7 +379,7 @@ __device__ __forceinline__ void dma_tile(const HeadView &hv, const StepView &sv,
     Cl[off] = acc[i][j][r];
   });
 
-  epilogue_from_lds<BM, BN, CP, TEXT, KSPLIT>(hv, sv, C, rowp, m0, n0, M, N);
+  epilogue_from_lds<BM, BN, CP, true, KSPLIT>(hv, sv, C, nullptr, 0, n0, M, N);
 }
 
 }  // namespace
