@@ -53,9 +53,9 @@ CSRC = os.path.join(ROOT, "paper_2607_02119_amd", "csrc")
 MEASURED_TRAFFIC = {
     # workload: dict(sources=[...], sha256=..., fetch_bytes=..., write_bytes=..., profile=...)
     "weight_streaming": dict(
-        sources=["k_stream.hip", "stream_tile.h", "gemm_common.h"],
-        sha256="94f40a0df98a9499182f4752cf032ebceebce6b0cc4b38870b52a7302311baa4",
-        fetch_bytes=277193728, write_bytes=8388608,
+        sources=["k_stream.hip", "pc_tile.h", "stream_tile.h", "gemm_common.h"],
+        sha256="29b0352b3b2e035e65774b85691acb4a12159f8286036adf646d3b6d2ab4e83e",
+        fetch_bytes=277099520, write_bytes=8388608,
         profile="profiles/head_step_weight_streaming.md"),
 }
 
