@@ -4,6 +4,8 @@ arguments and inconsistent batches before any launch."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -230,3 +232,27 @@ def test_empty_batch_is_a_no_op():
         rc = f(h, ctypes.byref(a), None)
         assert rc == mcd.MCD_OK, (name, mcd.mcd_last_error())
     mcd.mcd_head_destroy(h)
+
+
+def test_host_calls_on_a_torch_without_gpu_support():
+    """The host-only parts (plan, phases, scheduler) need no GPU function of torch, not even one
+    looked up when the module is imported."""
+    code = """
+import torch
+for name in [n for n in dir(torch._C) if n.startswith("_cuda_")]:
+    delattr(torch._C, name)
+from paper_2607_02119_amd import mcd
+import numpy as np
+h = mcd.mcd_head_create(H=64, K=3, V=50, pad_id=50, delays=[0, 1, 2], dtype=mcd.MCD_BF16, W=0x10000)
+plan, c = mcd.mcd_batch_plan(h, [1, 0, -1], [0, 1, 2])
+assert (c.n_pairs, c.n_solo) == (1, 1)
+mcd.mcd_head_destroy(h)
+s = mcd.Scheduler(4, 64, 1, 2)
+s.submit(2.0, 3, 0, 5)
+assert s.plan()["n_rows"] == 2
+emit = mcd.mcd_phase_advance([7], 9, 2, np.zeros(1, np.uint8), np.zeros(1, np.int32), [3], [1])
+assert list(emit) == [7]
+print("host calls ok")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0 and "host calls ok" in r.stdout, r.stderr
