@@ -10,7 +10,7 @@
 // cross-stream fork and join of every step.  Every tile runs exactly the code
 // of its own kernel, so the results are those of the two-launch path.
 #include "mfma2_tile.h"
-#include "stream_tile.h"
+#include "mixed_tile.h"
 
 namespace mcd {
 namespace {
@@ -33,31 +33,82 @@ hipError_t launch_mixed(const HeadView &hv, const StepView &sv, int n_audio, hip
   return hipGetLastError();
 }
 
+enum class Mixed { kTwoLaunches, kStreaming, kWideAudio };
+
+// Audio rows in 256 x 256 tiles (at least one full round of them) and text
+// rows in one row tile of 65..128 rows; streaming tiles for both otherwise.
+// Where the line lies (steps, H 4096): 768 audio rows of 32768 columns with
+// 128 text rows of 151936 take 455 us so and 465 in streaming tiles; 512 with
+// 24 text rows 339 in streaming tiles and 374 with 256 x 256 audio tiles.
+Mixed mixed_form(int32_t Mg, int32_t N, int32_t n_text) {
+  if (Mg < 1 || n_text < 1 || n_text > 128) return Mixed::kTwoLaunches;
+  const int64_t n_audio = tiles_256(Mg, N);
+  if (Mg <= 128 || n_text <= 64 || n_audio < 256)
+    return n_audio > (1 << 18) ? Mixed::kTwoLaunches : Mixed::kStreaming;
+  return n_audio > (1 << 20) ? Mixed::kTwoLaunches : Mixed::kWideAudio;
+}
+
+// Columns of the text tiles beside 256 x 256 audio tiles: narrow where 128
+// columns make less than one round, wide where they make more.
+int beside_wide_audio(int32_t V_text) {
+  const int t128 = (V_text + 127) / 128;
+  return t128 < 256 ? 64 : t128 == 256 ? 128 : 256;
+}
+
 }  // namespace
 
 hipError_t launch_mixed_gemm(const HeadView &hv, const StepView &sv, hipStream_t st,
                              bool *launched) {
-  *launched = false;
-  if (hv.dtype != MCD_BF16 || sv.Mg < 1 || sv.n_text < 1 || sv.n_text > 128) return hipSuccess;
-  // audio rows in 256 x 256 tiles (at least one full round of them) and text
-  // rows in one row tile of 65..128 rows; streaming tiles for both otherwise.
-  // Where the line lies (steps, H 4096): 768 audio rows of 32768 columns with
-  // 128 text rows of 151936 take 455 us so and 465 in streaming tiles; 512 with
-  // 24 text rows 339 in streaming tiles and 374 with 256 x 256 audio tiles.
-  const int64_t n_audio = tiles_256(sv.Mg, hv.N);
-  if (sv.Mg <= 128 || sv.n_text <= 64 || n_audio < 256) {
-    if (n_audio > (1 << 18)) return hipSuccess;
-    *launched = true;
-    if (sv.n_text <= 32) return launch_mixed_text_32(hv, sv, st);
-    return sv.n_text <= 64 ? launch_mixed_text_64(hv, sv, st) : launch_mixed_text_128(hv, sv, st);
+  const Mixed form = hv.dtype == MCD_BF16 ? mixed_form(sv.Mg, hv.N, sv.n_text) : Mixed::kTwoLaunches;
+  *launched = form != Mixed::kTwoLaunches;
+  if (form == Mixed::kTwoLaunches) return hipSuccess;
+  if (form == Mixed::kStreaming) {
+    switch (mixed_rows(sv.n_text)) {
+      case 32: return launch_mixed_text_32(hv, sv, st);
+      case 64: return launch_mixed_text_64(hv, sv, st);
+      default: return launch_mixed_text_128(hv, sv, st);
+    }
   }
-  if (n_audio > (1 << 20)) return hipSuccess;
-  *launched = true;
-  // the text tile width of the streaming launch for the same rows
-  const int t128 = (hv.V_text + 127) / 128;
-  if (t128 < 256) return launch_mixed<64>(hv, sv, (int)n_audio, st);
-  if (t128 == 256) return launch_mixed<128>(hv, sv, (int)n_audio, st);
-  return launch_mixed<256>(hv, sv, (int)n_audio, st);
+  const int n_audio = (int)tiles_256(sv.Mg, hv.N);
+  switch (beside_wide_audio(hv.V_text)) {
+    case 64: return launch_mixed<64>(hv, sv, n_audio, st);
+    case 128: return launch_mixed<128>(hv, sv, n_audio, st);
+    default: return launch_mixed<256>(hv, sv, n_audio, st);
+  }
+}
+
+ProjectionRoute projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text) {
+  ProjectionRoute r{0, {0, 0, 0}, {0, 0, 0}};
+  auto part = [&](int32_t M, int32_t cols, bool text) {   // of launch_head_gemm_part
+    ++r.launches;
+    return M <= 128 ? stream_tile(M, cols) : mfma_tile(M, cols, text);
+  };
+  switch (Mg > 0 && n_text > 0 ? mixed_form(Mg, N, n_text) : Mixed::kTwoLaunches) {
+    case Mixed::kStreaming: {
+      const int ra = mixed_rows(Mg), rt = mixed_rows(n_text);
+      const int ca = wide_audio(Mg, N) ? wide_columns(ra) : 64;
+      const int ct = wide_text(V_text) ? wide_columns(rt) : 64;
+      return ProjectionRoute{1, {ra, ca, stream_stages(ra, ca)}, {rt, ct, stream_stages(rt, ct)}};
+    }
+    case Mixed::kWideAudio: {
+      const int ct = beside_wide_audio(V_text);
+      const int stages = ct == 64 ? DmaShape<128, 64>::SW
+                         : ct == 128 ? DmaShape<128, 128>::SW : DmaShape<128, 256>::SW;
+      return ProjectionRoute{1, {256, 256, 0}, {128, ct, stages}};
+    }
+    case Mixed::kTwoLaunches: break;
+  }
+  if (Mg > 0) r.audio = part(Mg, N, false);
+  if (n_text > 0) r.text = part(n_text, V_text, true);
+  return r;
 }
 
 }  // namespace mcd
+
+extern "C" void mcd_projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text,
+                                     int32_t out[7]) {
+  const mcd::ProjectionRoute r = mcd::projection_route(Mg, N, n_text, V_text);
+  const int32_t w[7] = {r.launches,   r.audio.rows, r.audio.cols, r.audio.stages,
+                        r.text.rows,  r.text.cols,  r.text.stages};
+  for (int i = 0; i < 7; ++i) out[i] = w[i];
+}

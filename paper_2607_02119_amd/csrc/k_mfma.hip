@@ -282,16 +282,21 @@ hipError_t launch_mfma(const HeadView &hv, const StepView &sv, int M, int N, hip
 
 }  // namespace
 
-hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text, hipStream_t st) {
-  if (text) return launch_mfma<true>(hv, sv, sv.n_text, hv.V_text, st);
+StreamTile mfma_tile(int32_t M, int32_t N, bool text) {
+  if (text) return StreamTile{kMfmaBM, kMfmaBN, 0};
   // 256 x 256 tiles or the streaming path's, whichever needs less time.  A
   // round of 256 of the former takes about 730 in the unit of stream_cost (H
   // 4096: 132 us, against 139 for two rounds of 128 x 256 streaming tiles, 2 x
   // 384; 541 against 600 for four and eight), so they win where their last
   // round is more than half full (384 tiles in two rounds 257 us, 768
   // streaming tiles in three 235).
-  const int64_t wide = (tiles_256(sv.Mg, hv.N) + 255) / 256 * 730;
-  if (stream_cost(sv.Mg, hv.N) < wide) return launch_stream_gemm(hv, sv, false, st);
+  const int64_t wide = (tiles_256(M, N) + 255) / 256 * 730;
+  return stream_cost(M, N) < wide ? stream_tile(M, N) : StreamTile{256, 256, 0};
+}
+
+hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text, hipStream_t st) {
+  if (text) return launch_mfma<true>(hv, sv, sv.n_text, hv.V_text, st);
+  if (mfma_tile(sv.Mg, hv.N, false).stages) return launch_stream_gemm(hv, sv, false, st);
   return launch_mfma2(hv, sv, st);
 }
 

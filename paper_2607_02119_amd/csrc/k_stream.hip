@@ -28,60 +28,70 @@ hipError_t launch_pc(const HeadView &hv, const StepView &sv, int M, int N, hipSt
   return hipGetLastError();
 }
 
-// Up to 32 rows the hidden states are few and the weights' HBM reads bound the
-// tile: 64-column tiles when 128-column ones would leave compute units idle,
-// else 128-column ones.
-template <bool TEXT>
-hipError_t launch_few_rows(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
-  if ((N + 127) / 128 < 256) return launch_pc<32, 64, TEXT>(hv, sv, M, N, st);
-  return launch_pc<32, wide_columns(32), TEXT>(hv, sv, M, N, st);
+template <int BM, int BN>
+constexpr StreamTile tile_of() {
+  return StreamTile{BM, BN, PcShape<BM, BN>::SW};
 }
 
-// More rows: a tile takes in (BM + BN) x H x 2 bytes, and that rate bounds it,
+// More than 32 rows: a tile takes in (BM + BN) x H x 2 bytes, and that rate bounds it,
 // so a launch takes about rounds of 256 compute units x (BM + BN).  The shape
 // with the least of that; the larger of equals (fewer re-reads).  Measured (H
 // 4096, us, 32 x 64 / 64 x 64 / 64 x 96 / 128 x 64 tiles, the choice marked):
 // 128 rows of 2048 columns 18.0* / 21.6 / 27.1 / 29.1; of 8192 32.7 / 26.7* /
 // 29.0 / 32.1; of 12288 44.8 / 44.8 / 29.5* / 33.7; of 16384 61.5 / 49.9 / 56.0
 // / 38.8*; of 32768 54 with 128 x 128; 512 rows of 16384 70 with 128 x 256.
-struct TileShape {
-  int bm, bn;
-};
-constexpr TileShape kShapes[] = {{128, 256}, {128, 128}, {128, 64}, {64, 256},
-                                 {64, 128},  {64, 96},   {64, 64},  {32, 64}};
+constexpr StreamTile kShapes[] = {tile_of<128, 256>(), tile_of<128, 128>(), tile_of<128, 64>(),
+                                  tile_of<64, 256>(),  tile_of<64, 128>(),  tile_of<64, 96>(),
+                                  tile_of<64, 64>(),   tile_of<32, 64>()};
 
-int64_t cost_of(const TileShape &t, int M, int N) {
-  const int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-  return (tiles + 255) / 256 * (t.bm + t.bn);
+int64_t cost_of(const StreamTile &t, int M, int N) {
+  const int64_t tiles = (int64_t)((M + t.rows - 1) / t.rows) * ((N + t.cols - 1) / t.cols);
+  return (tiles + 255) / 256 * (t.rows + t.cols);
 }
 
-int best_shape(int M, int N) {
-  int best = -1;
-  for (int i = 0; i < (int)(sizeof kShapes / sizeof kShapes[0]); ++i) {
-    if (M <= 64 && kShapes[i].bm > 64) continue;   // rows of padding
-    if (best < 0 || cost_of(kShapes[i], M, N) < cost_of(kShapes[best], M, N)) best = i;
+const StreamTile &best_shape(int M, int N) {
+  const StreamTile *best = nullptr;
+  for (const StreamTile &t : kShapes) {
+    if (M <= 64 && t.rows > 64) continue;   // rows of padding
+    if (!best || cost_of(t, M, N) < cost_of(*best, M, N)) best = &t;
   }
-  return best;
+  return *best;
 }
 
 template <bool TEXT>
 hipError_t launch_tiles(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
-  if (M <= 32) return launch_few_rows<TEXT>(hv, sv, M, N, st);
-  switch (best_shape(M, N)) {
-    case 0: return launch_pc<128, 256, TEXT>(hv, sv, M, N, st);
-    case 1: return launch_pc<128, 128, TEXT>(hv, sv, M, N, st);
-    case 2: return launch_pc<128, 64, TEXT>(hv, sv, M, N, st);
-    case 3: return launch_pc<64, 256, TEXT>(hv, sv, M, N, st);
-    case 4: return launch_pc<64, 128, TEXT>(hv, sv, M, N, st);
-    case 5: return launch_pc<64, 96, TEXT>(hv, sv, M, N, st);
-    case 6: return launch_pc<64, 64, TEXT>(hv, sv, M, N, st);
+  const StreamTile t = stream_tile(M, N);
+  switch (t.rows * 1000 + t.cols) {
+    case 128256: return launch_pc<128, 256, TEXT>(hv, sv, M, N, st);
+    case 128128: return launch_pc<128, 128, TEXT>(hv, sv, M, N, st);
+    case 128064: return launch_pc<128, 64, TEXT>(hv, sv, M, N, st);
+    case 64256: return launch_pc<64, 256, TEXT>(hv, sv, M, N, st);
+    case 64128: return launch_pc<64, 128, TEXT>(hv, sv, M, N, st);
+    case 64096: return launch_pc<64, 96, TEXT>(hv, sv, M, N, st);
+    case 64064: return launch_pc<64, 64, TEXT>(hv, sv, M, N, st);
+    case 32128: return launch_pc<32, 128, TEXT>(hv, sv, M, N, st);
     default: return launch_pc<32, 64, TEXT>(hv, sv, M, N, st);
   }
 }
 
 }  // namespace
 
-int64_t stream_cost(int32_t M, int32_t N) { return cost_of(kShapes[best_shape(M, N)], M, N); }
+int64_t stream_cost(int32_t M, int32_t N) { return cost_of(best_shape(M, N), M, N); }
+
+// Up to 32 rows the hidden states are few and the weights' HBM reads bound the
+// tile: 64-column tiles when 128-column ones would leave compute units idle,
+// else 128-column ones.
+StreamTile stream_tile(int32_t M, int32_t N) {
+  if (M > 32) return best_shape(M, N);
+  return (N + 127) / 128 < 256 ? tile_of<32, 64>() : tile_of<32, wide_columns(32)>();
+}
+
+int32_t stream_stages(int rows, int cols) {
+  if (rows == 32 && cols == 128) return tile_of<32, 128>().stages;
+  for (const StreamTile &t : kShapes)
+    if (t.rows == rows && t.cols == cols) return t.stages;
+  return 0;
+}
 
 hipError_t launch_stream_gemm(const HeadView &hv, const StepView &sv, bool text,
                               hipStream_t st) {

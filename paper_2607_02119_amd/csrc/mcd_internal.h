@@ -81,13 +81,26 @@ hipError_t launch_head_gemm_part(const HeadView &hv, const StepView &sv, bool te
 hipError_t launch_stream_gemm(const HeadView &hv, const StepView &sv, bool text,
                               hipStream_t stream);
 int64_t stream_cost(int32_t M, int32_t N);
+// a projection's tile, and the 64-k slices its weight ring holds (streaming tiles)
+struct StreamTile {
+  int32_t rows, cols, stages;
+};
+StreamTile stream_tile(int32_t M, int32_t N);          // of launch_stream_gemm
+int32_t stream_stages(int rows, int cols);             // of one of its shapes, else 0
+StreamTile mfma_tile(int32_t M, int32_t N, bool text);  // of launch_mfma_gemm
 hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text,
                             hipStream_t stream);     // any number of rows
 // A batch of audio rows and at most 128 text rows: both projections in one
 // launch; *launched is false (and nothing is launched) for other batches.
 hipError_t launch_mixed_gemm(const HeadView &hv, const StepView &sv, hipStream_t st,
                              bool *launched);
-// its streaming tiles, by text rows (one file each: many tile shapes)
+// How a bf16 step's projections run: launches (0 to 2) and the tiles of its parts.
+struct ProjectionRoute {
+  int32_t launches;
+  StreamTile audio, text;
+};
+ProjectionRoute projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text);
+// streaming tiles of a mixed launch, by text rows (one file each: many tile shapes)
 hipError_t launch_mixed_text_32(const HeadView &hv, const StepView &sv, hipStream_t st);
 hipError_t launch_mixed_text_64(const HeadView &hv, const StepView &sv, hipStream_t st);
 hipError_t launch_mixed_text_128(const HeadView &hv, const StepView &sv, hipStream_t st);
@@ -112,3 +125,8 @@ hipError_t launch_interleave(const int32_t *grid, int32_t n_req, int32_t F, int3
                              hipStream_t stream);
 
 }  // namespace mcd
+
+// The route of a bf16 step as {launches, audio rows, columns, stages, text rows, columns, stages}
+// (0: no such part, or no streaming tile): for the tests, which have to reach every tile.
+extern "C" void mcd_projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text,
+                                     int32_t out[7]);

@@ -34,12 +34,17 @@ hipError_t launch_mixed_pc(const HeadView &hv, const StepView &sv, hipStream_t s
   return hipGetLastError();
 }
 
+inline bool wide_audio(int32_t Mg, int32_t N) { return Mg > 128 || (N + 127) / 128 >= 256; }
+inline bool wide_text(int32_t V_text) { return (V_text + 127) / 128 >= 256; }
+// rows of a part's tiles
+inline int mixed_rows(int32_t M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
+
 // Tile widths as the parts' own launches choose them: 64 columns where
 // 128-column tiles are fewer than the compute units, wide ones otherwise;
 // audio rows beyond 128 in 128 x 256 row tiles.
 template <int BMA, int BMT>
 hipError_t launch_mixed_rows(const HeadView &hv, const StepView &sv, hipStream_t st) {
-  const bool wa = sv.Mg > 128 || (hv.N + 127) / 128 >= 256, wt = (hv.V_text + 127) / 128 >= 256;
+  const bool wa = wide_audio(sv.Mg, hv.N), wt = wide_text(hv.V_text);
   constexpr int WA = wide_columns(BMA), WT = wide_columns(BMT);
   if (wa) return wt ? launch_mixed_pc<BMA, WA, BMT, WT>(hv, sv, st)
                     : launch_mixed_pc<BMA, WA, BMT, 64>(hv, sv, st);
@@ -49,9 +54,11 @@ hipError_t launch_mixed_rows(const HeadView &hv, const StepView &sv, hipStream_t
 
 template <int BMT>
 hipError_t launch_mixed_text(const HeadView &hv, const StepView &sv, hipStream_t st) {
-  if (sv.Mg <= 32) return launch_mixed_rows<32, BMT>(hv, sv, st);
-  if (sv.Mg <= 64) return launch_mixed_rows<64, BMT>(hv, sv, st);
-  return launch_mixed_rows<128, BMT>(hv, sv, st);
+  switch (mixed_rows(sv.Mg)) {
+    case 32: return launch_mixed_rows<32, BMT>(hv, sv, st);
+    case 64: return launch_mixed_rows<64, BMT>(hv, sv, st);
+    default: return launch_mixed_rows<128, BMT>(hv, sv, st);
+  }
 }
 
 }  // namespace

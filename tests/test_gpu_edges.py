@@ -18,6 +18,8 @@ from paper_2607_02119_amd import harness, mcd  # noqa: E402
 from tests.test_gpu_graph import (  # noqa: E402
     test_step_replayed_from_a_graph_equals_eager as replay)
 
+from tests._route import route, shape  # noqa: E402
+
 GAP_TOL, TOPK_TOL, TOPP_TOL = 1e-3, 1e-4, 1e-5
 
 
@@ -144,52 +146,60 @@ def test_topk_infinite_scores_give_valid_ids(V, K, Rs, top_p):
     assert g[0, 1] == 11 and g[1, 1] % 2 == 1
 
 
-# streaming tiles (copying and computing waves apart): 32, 64 and 128 rows by
-# 64, 128 (exactly 256 of them) and 256 columns, audio and text, at the edges
-# of their rows and columns; fewer slices of 64 k than ring stages, an odd
-# number of slices, and slice counts around the hidden rows' register buffers
+# streaming tiles (copying and computing waves apart) at the edges of their
+# rows and columns, audio and text; fewer slices of 64 k than ring stages, an
+# odd number of slices, and slice counts around the hidden rows' register
+# buffers (test_gpu_rings.py: more slices than ring stages, for every tile)
 STREAM = [
-    # H, V, K, pairs, solo, text, V_text
-    (64, 33, 1, 16, 0, 1, 65),
-    (64, 4096, 8, 16, 1, 0, 0),
-    (192, 4096, 8, 32, 0, 0, 0),
-    (448, 4096, 8, 64, 0, 0, 0),
-    (576, 61, 3, 32, 1, 33, 129),
-    (832, 64, 2, 63, 2, 64, 63),
-    (128, 4096, 9, 15, 1, 32, 33001),
-    (960, 4096, 9, 1, 0, 0, 0),
-    (320, 4093, 9, 20, 24, 65, 32801),
-    (64, 300, 2, 64, 1, 128, 257),
-    (704, 1027, 3, 70, 13, 0, 0),
+    # H, V, K, pairs, solo, text, V_text      audio tile, text tile
+    (64, 33, 1, 16, 0, 1, 65, "32x64", "32x64"),
+    (64, 4096, 8, 16, 1, 0, 0, "64x128", None),
+    (192, 4096, 8, 32, 0, 0, 0, "64x128", None),
+    (448, 4096, 8, 64, 0, 0, 0, "128x128", None),
+    (576, 61, 3, 32, 1, 33, 129, "128x64", "64x64"),
+    (832, 64, 2, 63, 2, 64, 63, "128x64", "64x64"),
+    (128, 4096, 9, 15, 1, 32, 33001, "32x128", "32x128"),
+    (960, 4096, 9, 1, 0, 0, 0, "32x128", None),
+    (320, 4093, 9, 20, 24, 65, 32801, "64x256", "128x256"),
+    (64, 300, 2, 64, 1, 128, 257, "128x256", "128x64"),
+    (704, 1027, 3, 70, 13, 0, 0, "32x64", None),
 ]
 
 
-@pytest.mark.parametrize("H,V,K,pairs,solo,text,V_text", STREAM)
-def test_streaming_tile_edges(H, V, K, pairs, solo, text, V_text):
+def check_tiles(wl, audio, text):
+    """The batch takes the tiles it stands for."""
+    r = route(2 * wl.n_pairs + wl.n_solo, wl.N, wl.n_text, wl.V_text)
+    assert (audio is None or shape(r.audio) == audio) and (text is None or shape(r.text) == text), r
+
+
+@pytest.mark.parametrize("H,V,K,pairs,solo,text,V_text,audio_tile,text_tile", STREAM)
+def test_streaming_tile_edges(H, V, K, pairs, solo, text, V_text, audio_tile, text_tile):
     wl = inputs.Workload(f"stream_{H}_{V}", H=H, K=K, V=V, n_pairs=pairs, n_solo=solo, n_text=text,
                          V_text=V_text, dtype="bf16", top_k=5, steps=2 * K, shuffle=True,
                          bias=V % 2 == 1)
     say(f"case {wl.name} R={wl.R} N={wl.N}")
+    check_tiles(wl, audio_tile, text_tile)
     check_one_step(wl, K, 1e-5)
 
 
 # audio rows beyond 128: whole rounds of 256 x 256 tiles against 128 x 256 ones
 # (the last round of the former full, half full and empty)
 ROWS = [
-    # V, K, pairs, solo
-    (4096, 8, 128, 0),
-    (4096, 8, 256, 0),
-    (4096, 8, 256, 1),
-    (4096, 6, 256, 256),
-    (3000, 5, 65, 30),
+    # V, K, pairs, solo, tile
+    (4096, 8, 128, 0, "128x256"),
+    (4096, 8, 256, 0, "256x256"),
+    (4096, 8, 256, 1, "128x256"),
+    (4096, 6, 256, 256, "128x256"),
+    (3000, 5, 65, 30, "128x128"),
 ]
 
 
-@pytest.mark.parametrize("V,K,pairs,solo", ROWS)
-def test_row_tile_choice(V, K, pairs, solo):
+@pytest.mark.parametrize("V,K,pairs,solo,tile", ROWS)
+def test_row_tile_choice(V, K, pairs, solo, tile):
     wl = inputs.Workload(f"rows_{V}_{K}_{pairs}", H=128, K=K, V=V, n_pairs=pairs, n_solo=solo,
                          dtype="bf16", top_k=5, steps=2 * K, shuffle=True)
     say(f"case {wl.name} R={wl.R} N={wl.N}")
+    check_tiles(wl, tile, None)
     check_one_step(wl, K, 1e-5)
 
 
@@ -270,25 +280,27 @@ def test_delay_pattern_rows(n_req, K, F, delays, shift):
 # the tile shape chosen by rounds x (rows + columns), each shape with ragged
 # rows and columns and with several row tiles (runs per XCD of unequal length)
 SHAPES = [
-    # V, K, pairs, solo, text, V_text         audio tile (text tile)
-    (1003, 7, 37, 21, 0, 0),                # 64 x 64, two row tiles
-    (4095, 3, 64, 0, 0, 0),                 # 64 x 96, two row tiles
-    (4001, 6, 20, 0, 0, 0),                 # 64 x 96
-    (4096, 2, 100, 0, 0, 0),                # 128 x 64, two row tiles
-    (4093, 2, 140, 20, 0, 0),               # 128 x 128, three row tiles
-    (4003, 5, 40, 20, 0, 0),                # 128 x 128
-    (2001, 1, 65, 0, 0, 0),                 # 32 x 64, five row tiles
-    (257, 1, 250, 3, 0, 0),                 # 32 x 64, sixteen row tiles
-    (10, 1, 0, 0, 95, 7021),                # text alone: 64 x 64
-    (10, 1, 0, 0, 120, 12290),              # 64 x 96
-    (10, 1, 0, 0, 40, 2000),                # 32 x 64, two row tiles
+    # V, K, pairs, solo, text, V_text         audio tile, text tile
+    (1003, 7, 37, 21, 0, 0, "64x64", None),        # two row tiles
+    (4095, 3, 64, 0, 0, 0, "64x96", None),         # two row tiles
+    (4001, 6, 20, 0, 0, 0, "64x96", None),
+    (4096, 2, 100, 0, 0, 0, "128x64", None),       # two row tiles
+    (4093, 2, 140, 20, 0, 0, "128x128", None),     # three row tiles
+    (4003, 5, 40, 20, 0, 0, "128x128", None),
+    (2001, 1, 65, 0, 0, 0, "32x64", None),         # five row tiles
+    (257, 1, 250, 3, 0, 0, "32x64", None),         # sixteen row tiles
+    (10, 1, 0, 0, 95, 7021, None, "64x64"),
+    (10, 1, 0, 0, 120, 12290, None, "128x64"),     # past one round of 64 x 96
+    (10, 1, 0, 0, 120, 12280, None, "64x96"),      # two row tiles, the last 8 columns short
+    (10, 1, 0, 0, 40, 2000, None, "32x64"),        # two row tiles
 ]
 
 
-@pytest.mark.parametrize("V,K,pairs,solo,text,V_text", SHAPES)
-def test_tile_shapes(V, K, pairs, solo, text, V_text):
+@pytest.mark.parametrize("V,K,pairs,solo,text,V_text,audio_tile,text_tile", SHAPES)
+def test_tile_shapes(V, K, pairs, solo, text, V_text, audio_tile, text_tile):
     wl = inputs.Workload(f"shape_{V}_{K}_{pairs}_{text}", H=128, K=K, V=V, n_pairs=pairs,
                          n_solo=solo, n_text=text, V_text=V_text, dtype="bf16", top_k=5,
                          steps=2 * K + 1, shuffle=True)
     say(f"case {wl.name} R={wl.R} N={wl.N}")
+    check_tiles(wl, audio_tile, text_tile)
     check_one_step(wl, K, 1e-5)
