@@ -19,8 +19,8 @@ namespace {
 // L2, but behind the weights' HBM reads in the compute unit's in-order return
 // path, so every byte takes 1.5 - 2 us under load, and a rate of 100 GB/s per
 // compute unit needs 150 - 200 KiB under way, more than the LDS holds.  The
-// registers of the loading waves hold the hidden rows' part of it, the whole
-// LDS the weights' part; neither costs the computing waves a stall, where a
+// registers of the loading waves hold the hidden rows' part of it, the LDS the
+// weights' part; neither costs the computing waves a stall, where a
 // wave that also computes adds its copies and LDS writes to its MFMAs.
 //
 // The computing waves split a slice by columns and k: KSPLIT k groups of
@@ -46,8 +46,17 @@ struct PcShape {
   static constexpr int kBudget = (BM == 32 && BN <= 128 ? 80 : 160) * 1024;
   static constexpr int SA = BN == 64 ? 3 : 2;
   static constexpr int HL = BM == 128 ? 6 : 8;   // hidden slices in flight in registers
-  static constexpr int SW0 = (kBudget - SA * AST) / WST, SWV = 63 / WIW + 1;   // counter range
-  static constexpr int SW = SW0 < SWV ? SW0 : SWV;
+  // Of the up to 16 weight stages that fit, at most six in the smaller tiles and
+  // eight in the others: the weight waves fill the ring before the first hidden
+  // rows are asked for, which then return behind it, and a tile of few slices
+  // waits for both.  All that fit / eight / six, us, at H 1024, 1600, 4096: 64
+  // rows of 16384 columns (64 x 64) 11.5 / 10.8 / 10.3, 14.6 / 14.0 / 13.5, 29.1
+  // / 28.9 / 28.0; 200 of 8192 (128 x 64) 12.6 / 11.7 / 11.7, 16.7 / 15.2 / 15.1,
+  // 30.3 / 28.9 / 29.7; 64 of 32768 (64 x 128, eight fit) at H 1600 - / 21.6 /
+  // 22.1.
+  static constexpr int SW0 = (kBudget - SA * AST) / WST;
+  static constexpr int SWM = BM * BN < 128 * 64 ? 6 : 8, SWV = 63 / WIW + 1;   // counter range
+  static constexpr int SW1 = SW0 < SWM ? SW0 : SWM, SW = SW1 < SWV ? SW1 : SWV;
   static constexpr int CP = BN + 4;        // padded row pitch of the sums (floats)
   static constexpr int kRing = SW * WST + SA * AST;
   static constexpr int kParams = (BM / 2) * 16;

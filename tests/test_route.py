@@ -34,3 +34,10 @@ def test_parts_alone_and_many_text_rows():
     assert shape(route(512, 32768).audio) == "256x256"
     r = route(25, 111, 150, 300)          # more than 128 text rows: two launches
     assert r.launches == 2 and shape(r.text) == "256x128"
+
+
+@pytest.mark.parametrize("tile,most", [("32x64", 6), ("64x64", 6), ("64x96", 6), ("128x64", 8)])
+def test_weight_rings_of_small_tiles_stay_short(tile, most):
+    """A longer ring holds back the first hidden rows: 64 rows of 16384 columns at H 1024 took
+    11.5 us with all the stages that fit and 10.3 with six (10.3 in the four-wave tile before)."""
+    assert route(*alone_sizes(tile, False)).audio.stages <= most
