@@ -35,17 +35,33 @@ hipError_t launch_mixed(const HeadView &hv, const StepView &sv, int n_audio, hip
 
 enum class Mixed { kTwoLaunches, kStreaming, kWideAudio };
 
-// Audio rows in 256 x 256 tiles (at least one full round of them) and text
-// rows in one row tile of 65..128 rows; streaming tiles for both otherwise.
-// Where the line lies (steps, H 4096): 768 audio rows of 32768 columns with
-// 128 text rows of 151936 take 455 us so and 465 in streaming tiles; 512 with
-// 24 text rows 339 in streaming tiles and 374 with 256 x 256 audio tiles.
-Mixed mixed_form(int32_t Mg, int32_t N, int32_t n_text) {
+// More than 64 text rows (one row tile of 128) beside at least one round of 256
+// x 256 audio tiles: those two in one launch.  Where the line lies (steps, H
+// 4096): 768 audio rows of 32768 columns with 128 text rows of 151936 take 455
+// us so and 465 in streaming tiles.
+//
+// Fewer text rows beside two rounds or more of 256 x 256 audio tiles: two
+// launches, where their fork and join cost less than streaming audio tiles.
+// Streaming tiles for both / two launches, us, H 4096, then H 1600 or 1024:
+// 1024 rows of 32768 columns with 64 text rows of 151936 484 / 466, 224 / 234
+// (H 1600); 1536 with 64 622 / 581, 287 / 279 (H 1600); 1024 with 24 455 / 448;
+// 512 with 24 321 / 344; 1536 with 24 593 / 564.  A text part of less than a
+// round fills no gap of the audio tiles: 1024 rows with 8 text rows of 8000 275 /
+// 308, 1536 423 / 433, 2048 562 / 549, 211 / 188 (H 1024); 2048 with 64 of 32003
+// 605 / 594, 211 / 220 (H 1024).
+//
+// Streaming tiles in one launch otherwise.
+Mixed mixed_form(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text, int32_t H) {
   if (Mg < 1 || n_text < 1 || n_text > 128) return Mixed::kTwoLaunches;
   const int64_t n_audio = tiles_256(Mg, N);
-  if (Mg <= 128 || n_text <= 64 || n_audio < 256)
-    return n_audio > (1 << 18) ? Mixed::kTwoLaunches : Mixed::kStreaming;
-  return n_audio > (1 << 20) ? Mixed::kTwoLaunches : Mixed::kWideAudio;
+  if (Mg > 128 && n_text > 64 && n_audio >= 256)
+    return n_audio > (1 << 20) ? Mixed::kTwoLaunches : Mixed::kWideAudio;
+  const bool fills = text_fills(n_text, V_text);
+  if (n_text <= 64 && mfma_tile(Mg, N, false, fills).stages == 0 &&
+      (fills ? n_audio >= 768 || (n_audio >= 512 && H >= 2048)
+             : n_audio >= 1024 && (n_text <= 32 || H >= 1536)))
+    return Mixed::kTwoLaunches;
+  return n_audio > (1 << 18) ? Mixed::kTwoLaunches : Mixed::kStreaming;
 }
 
 // Columns of the text tiles beside 256 x 256 audio tiles: narrow where 128
@@ -59,7 +75,9 @@ int beside_wide_audio(int32_t V_text) {
 
 hipError_t launch_mixed_gemm(const HeadView &hv, const StepView &sv, hipStream_t st,
                              bool *launched) {
-  const Mixed form = hv.dtype == MCD_BF16 ? mixed_form(sv.Mg, hv.N, sv.n_text) : Mixed::kTwoLaunches;
+  const Mixed form = hv.dtype == MCD_BF16
+                         ? mixed_form(sv.Mg, hv.N, sv.n_text, hv.V_text, hv.H)
+                         : Mixed::kTwoLaunches;
   *launched = form != Mixed::kTwoLaunches;
   if (form == Mixed::kTwoLaunches) return hipSuccess;
   if (form == Mixed::kStreaming) {
@@ -77,13 +95,15 @@ hipError_t launch_mixed_gemm(const HeadView &hv, const StepView &sv, hipStream_t
   }
 }
 
-ProjectionRoute projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text) {
+ProjectionRoute projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text,
+                                 int32_t H) {
   ProjectionRoute r{0, {0, 0, 0}, {0, 0, 0}};
+  const bool both = Mg > 0 && n_text > 0;
   auto part = [&](int32_t M, int32_t cols, bool text) {   // of launch_head_gemm_part
     ++r.launches;
-    return M <= 128 ? stream_tile(M, cols) : mfma_tile(M, cols, text);
+    return M <= 128 ? stream_tile(M, cols, text && both) : mfma_tile(M, cols, text, text_fills(n_text, V_text));
   };
-  switch (Mg > 0 && n_text > 0 ? mixed_form(Mg, N, n_text) : Mixed::kTwoLaunches) {
+  switch (both ? mixed_form(Mg, N, n_text, V_text, H) : Mixed::kTwoLaunches) {
     case Mixed::kStreaming: {
       const int ra = mixed_rows(Mg), rt = mixed_rows(n_text);
       const int ca = wide_audio(Mg, N) ? wide_columns(ra) : 64;
@@ -106,8 +126,8 @@ ProjectionRoute projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t 
 }  // namespace mcd
 
 extern "C" void mcd_projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text,
-                                     int32_t out[7]) {
-  const mcd::ProjectionRoute r = mcd::projection_route(Mg, N, n_text, V_text);
+                                     int32_t H, int32_t out[7]) {
+  const mcd::ProjectionRoute r = mcd::projection_route(Mg, N, n_text, V_text, H);
   const int32_t w[7] = {r.launches,   r.audio.rows, r.audio.cols, r.audio.stages,
                         r.text.rows,  r.text.cols,  r.text.stages};
   for (int i = 0; i < 7; ++i) out[i] = w[i];

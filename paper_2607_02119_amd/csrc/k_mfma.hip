@@ -282,7 +282,7 @@ hipError_t launch_mfma(const HeadView &hv, const StepView &sv, int M, int N, hip
 
 }  // namespace
 
-StreamTile mfma_tile(int32_t M, int32_t N, bool text) {
+StreamTile mfma_tile(int32_t M, int32_t N, bool text, bool filled) {
   if (text) return StreamTile{kMfmaBM, kMfmaBN, 0};
   // 256 x 256 tiles or the streaming path's, whichever needs less time.  A
   // round of 256 of the former takes about 730 in the unit of stream_cost (H
@@ -290,13 +290,17 @@ StreamTile mfma_tile(int32_t M, int32_t N, bool text) {
   // 384; 541 against 600 for four and eight), so they win where their last
   // round is more than half full (384 tiles in two rounds 257 us, 768
   // streaming tiles in three 235).
-  const int64_t wide = (tiles_256(M, N) + 255) / 256 * 730;
-  return stream_cost(M, N) < wide ? stream_tile(M, N) : StreamTile{256, 256, 0};
+  // Where text tiles fill that round it is worth its tiles (1280 rows of 32768
+  // columns in 640, with 24 text rows of 151936: 521 us in streaming tiles, 498
+  // so).
+  const int64_t tiles = tiles_256(M, N);
+  const int64_t wide = filled ? tiles * 730 / 256 : (tiles + 255) / 256 * 730;
+  return stream_cost(M, N) < wide ? stream_tile(M, N, false) : StreamTile{256, 256, 0};
 }
 
 hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text, hipStream_t st) {
   if (text) return launch_mfma<true>(hv, sv, sv.n_text, hv.V_text, st);
-  if (mfma_tile(sv.Mg, hv.N, false).stages) return launch_stream_gemm(hv, sv, false, st);
+  if (mfma_tile(sv.Mg, hv.N, false, text_fills(sv.n_text, hv.V_text)).stages) return launch_stream_gemm(hv, sv, false, st);
   return launch_mfma2(hv, sv, st);
 }
 

@@ -60,7 +60,9 @@ const StreamTile &best_shape(int M, int N) {
 
 template <bool TEXT>
 hipError_t launch_tiles(const HeadView &hv, const StepView &sv, int M, int N, hipStream_t st) {
-  const StreamTile t = stream_tile(M, N);
+  const StreamTile t = stream_tile(M, N, TEXT && sv.Mg > 0);
+  if constexpr (TEXT)
+    if (t.rows == 32 && t.cols == 256) return launch_pc<32, 256, TEXT>(hv, sv, M, N, st);
   switch (t.rows * 1000 + t.cols) {
     case 128256: return launch_pc<128, 256, TEXT>(hv, sv, M, N, st);
     case 128128: return launch_pc<128, 128, TEXT>(hv, sv, M, N, st);
@@ -80,9 +82,14 @@ int64_t stream_cost(int32_t M, int32_t N) { return cost_of(best_shape(M, N), M, 
 
 // Up to 32 rows the hidden states are few and the weights' HBM reads bound the
 // tile: 64-column tiles when 128-column ones would leave compute units idle,
-// else 128-column ones.
-StreamTile stream_tile(int32_t M, int32_t N) {
+// else 128-column ones.  Beside audio tiles of another launch, which take a
+// compute unit's whole LDS, tiles that take all of it too: two of the smaller
+// ones leave a unit at different times, and it stands half empty until both
+// have (24 text rows of 151936 beside 1024 / 2048 audio rows of 32768, H 4096:
+// 471 / 727 us with 128-column tiles, 443 / 689 with 256).
+StreamTile stream_tile(int32_t M, int32_t N, bool beside) {
   if (M > 32) return best_shape(M, N);
+  if (beside) return tile_of<32, 256>();
   return (N + 127) / 128 < 256 ? tile_of<32, 64>() : tile_of<32, wide_columns(32)>();
 }
 

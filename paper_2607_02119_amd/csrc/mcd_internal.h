@@ -85,9 +85,16 @@ int64_t stream_cost(int32_t M, int32_t N);
 struct StreamTile {
   int32_t rows, cols, stages;
 };
-StreamTile stream_tile(int32_t M, int32_t N);          // of launch_stream_gemm
+// of launch_stream_gemm; beside: text rows beside audio rows in a launch of their own
+StreamTile stream_tile(int32_t M, int32_t N, bool beside);
 int32_t stream_stages(int rows, int cols);             // of one of its shapes, else 0
-StreamTile mfma_tile(int32_t M, int32_t N, bool text);  // of launch_mfma_gemm
+// of launch_mfma_gemm; filled: text tiles run in the last round of audio tiles
+StreamTile mfma_tile(int32_t M, int32_t N, bool text, bool filled);
+// At most 64 text rows of at least a round of 256-column tiles (in two launches
+// beside audio rows they fill the round that these leave part empty).
+inline bool text_fills(int32_t n_text, int32_t V_text) {
+  return n_text > 0 && n_text <= 64 && V_text > 255 * 256;
+}
 hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text,
                             hipStream_t stream);     // any number of rows
 // A batch of audio rows and at most 128 text rows: both projections in one
@@ -99,7 +106,7 @@ struct ProjectionRoute {
   int32_t launches;
   StreamTile audio, text;
 };
-ProjectionRoute projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text);
+ProjectionRoute projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text, int32_t H);
 // streaming tiles of a mixed launch, by text rows (one file each: many tile shapes)
 hipError_t launch_mixed_text_32(const HeadView &hv, const StepView &sv, hipStream_t st);
 hipError_t launch_mixed_text_64(const HeadView &hv, const StepView &sv, hipStream_t st);
@@ -129,4 +136,4 @@ hipError_t launch_interleave(const int32_t *grid, int32_t n_req, int32_t F, int3
 // The route of a bf16 step as {launches, audio rows, columns, stages, text rows, columns, stages}
 // (0: no such part, or no streaming tile): for the tests, which have to reach every tile.
 extern "C" void mcd_projection_route(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text,
-                                     int32_t out[7]);
+                                     int32_t H, int32_t out[7]);

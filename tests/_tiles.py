@@ -38,6 +38,14 @@ def wide_sizes(text):
     return 189, 65501, 95, {"128x64": 2001, "128x128": 32765, "128x256": 40957}[text]
 
 
+# audio rows and columns, text rows and columns of batches that run as two launches, and their
+# tiles: 256 x 256 audio tiles in at least three rounds beside a text part of a round or more, and
+# in four beside a smaller one
+TWO = [((765, 65501, 31, 65501), "256x256", "32x256"),
+       ((765, 65501, 61, 65501), "256x256", "64x256"),
+       ((1021, 65501, 31, 2001), "256x256", "32x256")]
+
+
 def wrapping_slices(stages):
     """A number of 64-k slices that takes a weight ring of `stages` round, and the hidden rows'
     ring and registers (at most 2 + 8 slices) too, ending in the middle of each."""

@@ -168,7 +168,7 @@ STREAM = [
 
 def check_tiles(wl, audio, text):
     """The batch takes the tiles it stands for."""
-    r = route(2 * wl.n_pairs + wl.n_solo, wl.N, wl.n_text, wl.V_text)
+    r = route(2 * wl.n_pairs + wl.n_solo, wl.N, wl.n_text, wl.V_text, wl.H)
     assert (audio is None or shape(r.audio) == audio) and (text is None or shape(r.text) == text), r
 
 

@@ -14,8 +14,8 @@ if not torch.cuda.is_available():
 
 from paper_2607_02119_amd import mcd  # noqa: E402
 from tests._route import route  # noqa: E402
-from tests._tiles import (ALONE, MIXED, WIDE, alone_sizes, mixed_sizes, wide_sizes,  # noqa: E402
-                          wrapping_slices)
+from tests._tiles import (  # noqa: E402
+    ALONE, MIXED, TWO, WIDE, alone_sizes, mixed_sizes, wide_sizes, wrapping_slices)
 
 # bf16 products are exact in fp32.  A fp32 sum of n of them, of variance 1 / n each, has rounding
 # errors of standard deviation about sqrt(n) 2^-24 / 2 in any order: 1e-6 at n = 1216, and the
@@ -106,3 +106,8 @@ def test_mixed_launch(audio, text):
 @pytest.mark.parametrize("text", WIDE)
 def test_beside_wide_audio(text):
     check(*wide_sizes(text))
+
+
+@pytest.mark.parametrize("sizes,audio,text", TWO)
+def test_two_launches(sizes, audio, text):
+    check(*sizes)

@@ -5,7 +5,7 @@ import pytest
 pytest.importorskip("paper_2607_02119_amd.mcd", reason="libmcd.so not built")
 
 from tests._route import route, shape  # noqa: E402
-from tests._tiles import ALONE, MIXED, WIDE, alone_sizes, mixed_sizes, wide_sizes  # noqa: E402
+from tests._tiles import ALONE, MIXED, TWO, WIDE, alone_sizes, mixed_sizes, wide_sizes  # noqa: E402
 
 
 @pytest.mark.parametrize("text", [False, True])
@@ -27,6 +27,39 @@ def test_mixed_tiles_are_reached(audio, text):
 def test_text_tiles_beside_wide_audio_are_reached(text):
     r = route(*wide_sizes(text))
     assert (r.launches, shape(r.audio), shape(r.text)) == (1, "256x256", text)
+
+
+@pytest.mark.parametrize("sizes,audio,text", TWO)
+def test_two_launches_are_reached(sizes, audio, text):
+    r = route(*sizes, H=832)
+    assert (r.launches, shape(r.audio), shape(r.text)) == (2, audio, text)
+
+
+# audio rows (of 32768 columns), text rows, text columns, H: launches.  Measured as one launch of
+# streaming tiles and as two, us: see the numbers.
+FORMS = [
+    (512, 24, 151936, 4096, 1),      # 321 / 344
+    (512, 64, 151936, 4096, 1),      # 352 / 358
+    (1024, 24, 151936, 4096, 2),     # 455 / 448
+    (1024, 64, 151936, 4096, 2),     # 484 / 466
+    (1024, 64, 151936, 1600, 1),     # 224 / 234
+    (1280, 24, 151936, 4096, 2),     # 527 / 516
+    (1536, 64, 151936, 4096, 2),     # 622 / 581
+    (1536, 64, 151936, 1600, 2),     # 287 / 279
+    (2048, 24, 151936, 4096, 2),     # 734 / 699
+    (640, 24, 151936, 4096, 1),      # 256 x 256 tiles would be one sixth padding
+    (1024, 8, 8000, 4096, 1),        # 275 / 308
+    (2048, 8, 8000, 4096, 2),        # 562 / 549
+    (2048, 8, 8000, 1024, 2),        # 211 / 188
+    (2048, 64, 32003, 1024, 1),      # 211 / 220
+]
+
+
+@pytest.mark.parametrize("rows,text,V_text,H,launches", FORMS)
+def test_few_text_rows_beside_many_audio_rows(rows, text, V_text, H, launches):
+    r = route(rows, 32768, text, V_text, H)
+    assert r.launches == launches
+    assert shape(r.audio) == ("256x256" if launches == 2 else "128x256")
 
 
 def test_parts_alone_and_many_text_rows():
