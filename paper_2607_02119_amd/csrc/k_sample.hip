@@ -1308,19 +1308,23 @@ __device__ __forceinline__ int topk_by_list(const float (&x)[4 * GPT], int top_k
   for (int j = 0; j < 4; ++j) lo = fminf(lo, m[j] > -INFINITY ? m[j] : INFINITY);
   lo = wave_min(lo);
   // NaN, +inf, nothing but -inf, or a range past fp32: not here
-  if (!(mx > -INFINITY && mx - lo <= 3.0e38f)) return -1;
+  if (!(mx > -INFINITY && mx - lo < INFINITY)) return -1;
   float bound = -3.4028234664e38f;         // every finite score
   if (wave_count<4>([&](int j) { return m[j] > -INFINITY; }) >= top_k) {
     // at least k maxima reach `bound` throughout; eight halvings leave a few
-    // scores more than k above it
-    float hi = mx;
+    // scores more than k above it.  The first cut lies no lower than the bins
+    // reach: where a part holds nothing but masked ids (large negative scores),
+    // eight halvings of that range would end far below the scores (4096 vectors
+    // of 4096 ids, half of the 16-id blocks at -1e30, top-k 50: 42.3 us without,
+    // 24.0 with, 38.9 through the bins).
+    float hi = mx, mid = fmaxf(lo + 0.5f * (hi - lo), mx - kBins / kBinScale);
     bound = lo;
     for (int it = 0; it < 8; ++it) {
-      const float mid = bound + 0.5f * (hi - bound);
       const int c = wave_count<4>([&](int j) { return m[j] >= mid; });
       if (c >= top_k) bound = mid;
       else hi = mid;
       if (c == top_k) break;
+      mid = bound + 0.5f * (hi - bound);
     }
   }
   // groups with a score at or above the bound, to the list

@@ -93,6 +93,14 @@ TOPK = [
     (1024, 4, 256, 3.6, 0.125, 40, 0.9, 0.0, 0.0),
     (1003, 4, 256, 3.6, 0.0, 30, 0.9, 0.9, -1e30),
     (130, 8, 128, 2.0, 0.0, 129, 0.99, 0.0, 0.0),
+    # masked to the lowest fp32 value, to -1e30 and to -inf; unmasked scores
+    # below the first cut of the bound's search (32 under the maximum)
+    (4096, 2, 6, 2.0, 0.0, 50, 0.9, 0.995, -3.4028234663852886e38),
+    (1024, 4, 256, 2.0, 0.0, 20, 1.0, 0.95, -3.4028234663852886e38),
+    (2048, 2, 6, 2.0, 0.0, 50, 1.0, 0.99, -1e30),
+    (4096, 2, 6, 2.0, 0.0, 50, 0.9, 0.995, -np.inf),
+    (4096, 2, 6, 40.0, 0.0, 64, 1.0, 0.0, 0.0),
+    (1024, 4, 256, 40.0, 0.0, 50, 0.9, 0.9, -1e30),
 ]
 
 
