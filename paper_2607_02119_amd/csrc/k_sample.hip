@@ -746,12 +746,15 @@ __device__ __forceinline__ int find_cut_bin(const T *h, uint64_t target, uint64_
   return b;
 }
 
-// Bin of slot i (-1: not active), recomputed in every pass rather than held:
-// the array would set this kernel's register count, and with it how many
-// vectors a compute unit works on at a time.
-template <int GPT>
+// Bin of slot i (-1: not active).  Where the list holds any vector the bins are
+// for non-finite scores only, and are recomputed in every pass: held, they would
+// set the kernel's register count.  Recomputed in the other forms too they cost
+// 16 vectors of 4096 ids (k 128 / with p 0.9) 9.7 / 14.7 us against 8.9 / 12.9,
+// and 4096 vectors 39.1 / 59.1 against 37.3 / 53.0.
+template <int GPT, int TPV>
 __device__ __forceinline__ int bin_of(const float (&x)[4 * GPT], uint32_t active, float mx, int i) {
-  const float d = (mx - fresh(x[i])) * kBinScale;   // monotone in x
+  const float xi = GPT * TPV <= kListCap ? fresh(x[i]) : x[i];
+  const float d = (mx - xi) * kBinScale;   // monotone in x
   return ((active >> i) & 1) ? (d < (float)kBins ? (int)d : kBins) : -1;
 }
 
@@ -829,12 +832,12 @@ __device__ __forceinline__ void list_bin(Smem<TPV> &sm, const float (&x)[4 * GPT
   const int gt = Grp<TPV>::tid();
   uint32_t c = 0;
 #pragma unroll
-  for (int i = 0; i < EPL; ++i) c += bin_of<GPT>(x, active, mx, i) == bc ? 1u : 0u;
+  for (int i = 0; i < EPL; ++i) c += bin_of<GPT, TPV>(x, active, mx, i) == bc ? 1u : 0u;
   if (c == 0) return;
   uint32_t pos = atomicAdd(&sm.lcount, c);
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    if (bin_of<GPT>(x, active, mx, i) == bc) {
+    if (bin_of<GPT, TPV>(x, active, mx, i) == bc) {
       if (pos < (uint32_t)TPV) sm.le[pos] = {x[i], id_of<TPV>(i, gt), MASS ? mass_of(x[i], mx) : 0ull};
       ++pos;
     }
@@ -898,7 +901,7 @@ __device__ __forceinline__ uint32_t select_topk(const float (&x)[4 * GPT], uint3
   const int gt = Grp<TPV>::tid();
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int b = bin_of<GPT>(x, active, mx, i);
+    const int b = bin_of<GPT, TPV>(x, active, mx, i);
     if (b >= 0 && b < kBins) atomicAdd(&sm.u.cnt[b], 1u);
   }
   Grp<TPV>::sync();
@@ -909,7 +912,7 @@ __device__ __forceinline__ uint32_t select_topk(const float (&x)[4 * GPT], uint3
   if (bc < kBins && need == inbin) {
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      const int b = bin_of<GPT>(x, active, mx, i);
+      const int b = bin_of<GPT, TPV>(x, active, mx, i);
       if (b >= 0 && b <= bc) keep |= 1u << i;
     }
     return keep;
@@ -927,7 +930,7 @@ __device__ __forceinline__ uint32_t select_topk(const float (&x)[4 * GPT], uint3
   if (gt == 0) sm.lcount = 0;
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int b = bin_of<GPT>(x, active, mx, i);
+    const int b = bin_of<GPT, TPV>(x, active, mx, i);
     if (b >= 0 && b < bc) keep |= 1u << i;
   }
   return keep;
@@ -949,7 +952,7 @@ __device__ __forceinline__ uint32_t select_topp(const float (&x)[4 * GPT], uint3
   if constexpr (TPV == kWave) Grp<TPV>::sync();   // the clearing stores before the adds
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int b = bin_of<GPT>(x, active, mx, i);
+    const int b = bin_of<GPT, TPV>(x, active, mx, i);
     if (b >= 0) atomicAdd(&sm.u.mh[b], (unsigned long long)mass_of(x[i], mx));
   }
   Grp<TPV>::sync();
@@ -999,7 +1002,7 @@ __device__ __forceinline__ uint32_t select_topp(const float (&x)[4 * GPT], uint3
   if (gt == 0) sm.lcount = 0;
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int b = bin_of<GPT>(x, active, mx, i);
+    const int b = bin_of<GPT, TPV>(x, active, mx, i);
     if (b >= 0 && b < bc) keep |= 1u << i;
   }
   return keep;
@@ -1129,8 +1132,26 @@ __device__ __forceinline__ int draw_nucleus(const float (&x)[4 * GPT], uint32_t 
 // Against the histogram of every score this reads each score twice (a maximum
 // and a comparison) instead of computing its key, its bin and an LDS add, and
 // needs two barriers instead of six.  It does not serve vectors whose list
-// overflows (k above about 100, heavy ties at the bound) or whose scores are
-// not finite: those take the bins below, which give the same token.
+// overflows (heavy ties at the bound) or whose scores are not finite: those take
+// the bins below, which give the same token.  Larger cuts than list_limit go to
+// the bins at once, which then are cleared under the scores' loads.
+//
+// Largest top-k cut of the list.  256 maxima of 16 or 8 ids leave more scores
+// above the bound than maxima, so lists of 128 groups overflow from k of about
+// 100 on; with 4 ids per maximum, from 120; and never where the list holds the
+// whole vector.  At most 1024 ids in a workgroup, top-k with top-p: once the
+// groups exceed one per lane the bins are faster.  List / bins, us: 4096
+// vectors of 4096 ids k 96 25.6 / 37, k 112 44.2 / 37.3; 128 of 2048 k 96 6.9 /
+// 7.5, k 112 9.1 / 7.5; 8192 of 1024 k 120 23.7 / 25, k 128 29.0 / 25.2; 512 of
+// 1024 with p 0.9 k 50 8.3 / 9.6, k 64 10.3 / 9.6, k 112 11.2 / 9.7.
+template <int GPT, int TPV>
+__device__ __forceinline__ int list_limit(float top_p) {
+  if constexpr (GPT * TPV <= kListCap) return MCD_MAX_V;
+  if constexpr (TPV == kWave) return 120;
+  if constexpr (GPT == 1) return top_p < 1.0f ? 60 : 120;
+  return 96;
+}
+
 __device__ __forceinline__ float max_nan(float a, float b) {   // NaN if either is
   return __builtin_elementwise_maximum(a, b);
 }
@@ -1312,19 +1333,24 @@ __device__ __forceinline__ int topk_by_list(const float (&x)[4 * GPT], int top_k
   float bound = -3.4028234664e38f;         // every finite score
   if (wave_count<4>([&](int j) { return m[j] > -INFINITY; }) >= top_k) {
     // at least k maxima reach `bound` throughout; eight halvings leave a few
-    // scores more than k above it.  The first cut lies no lower than the bins
-    // reach: where a part holds nothing but masked ids (large negative scores),
-    // eight halvings of that range would end far below the scores (4096 vectors
-    // of 4096 ids, half of the 16-id blocks at -1e30, top-k 50: 42.3 us without,
-    // 24.0 with, 38.9 through the bins).
-    float hi = mx, mid = fmaxf(lo + 0.5f * (hi - lo), mx - kBins / kBinScale);
+    // scores more than k above it
+    float hi = mx;
     bound = lo;
+    // Where a part holds nothing but masked ids (large negative scores), halving
+    // that range would end far below the scores: a first cut at the bins' range
+    // (4096 vectors of 4096 ids, half of the 16-id blocks at -1e30, top-k 50:
+    // 42.3 us without it, 23.9 with, 38.9 through the bins).
+    const float first = mx - kBins / kBinScale;
+    if (lo < first) {
+      if (wave_count<4>([&](int j) { return m[j] >= first; }) >= top_k) bound = first;
+      else hi = first;
+    }
     for (int it = 0; it < 8; ++it) {
+      const float mid = bound + 0.5f * (hi - bound);
       const int c = wave_count<4>([&](int j) { return m[j] >= mid; });
       if (c >= top_k) bound = mid;
       else hi = mid;
       if (c == top_k) break;
-      mid = bound + 0.5f * (hi - bound);
     }
   }
   // groups with a score at or above the bound, to the list
@@ -1363,11 +1389,11 @@ __device__ __forceinline__ int topk_by_list(const float (&x)[4 * GPT], int top_k
   return draw_from_list<2, TPV>(sm, n, bound, mx, top_k, top_p, nk);
 }
 
-// The bins, lists and flags of the selection below, cleared for their first use.
+// The bins, lists and flags of the selection below, cleared for their first use
+// (published by its first group reduction).
 template <int TPV>
 __device__ __forceinline__ void clear_selection(Smem<TPV> &sm) {
   const int gt = Grp<TPV>::tid();
-  Grp<TPV>::sync();                        // the top-k list's readers are done
   for (int b = gt; b <= kBins; b += TPV) sm.u.cnt[b] = 0;
   sm.keepbits[gt] = 0;
   set_sentinel<TPV>(sm.le[gt]);
@@ -1464,7 +1490,8 @@ __device__ __forceinline__ int select_and_draw(const StepView &sv, const float (
 // noise key, reductions), so the kernel is as fast as many vectors are in
 // flight.  4096 vectors of 4096 ids (top-k 50): 30.9 us at four waves, 27.7 at
 // five, 26.9 at six, 27.5 at eight (which spills in every path); 8192 vectors
-// of 1024 ids: 18.1, 18.2, 17.0.  Two registers of the radix fallback spill.
+// of 1024 ids: 18.1, 18.2, 17.0.  Of the 80 registers then,
+// five more spill in the bins and the radix fallback (4096 ids).
 template <int GPT, int TPV>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) void sample_kernel(HeadView hv, StepView sv,
                                                           int with_text) {
@@ -1598,6 +1625,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
     if (bad) {
       if (gt == 0) atomicOr(sv.status, (uint32_t)MCD_DEV_BAD_PARAM);
     } else {
+      const bool cut = T != 0.0f && top_k > 0 && top_k < V;
+      const bool list = cut && top_k <= list_limit<GPT, TPV>(P);
+      if (cut && !list) clear_selection<TPV>(sm);
       // The vector's noise key (64-bit multiplies on uniform values).  A
       // one-wave group derives it on the vector unit (a shorter chain than the
       // scalar unit's 32-bit halves).  In a workgroup group the first wave
@@ -1617,7 +1647,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
           sm.nkw[4] = w0.c3;
         }
       }
-      if (T != 0.0f && !(top_k > 0 && top_k < V)) {
+      if (T != 0.0f && !cut) {
         // no top-k cut: candidates in perturbed-score order tested against the
         // nucleus (the noise of every id)
         Grp<TPV>::sync();
@@ -1625,9 +1655,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) v
           nk = NoiseKey{sm.nkw[0], sm.nkw[1], sm.nkw[2], sm.nkw[3], sm.nkw[4]};
         token = draw_nucleus<GPT, TPV>(x, active, nk, P, sm, slot);
       } else {
-        token = T != 0.0f ? topk_by_list<GPT, TPV>(x, top_k, P, nk, sm) : -1;
+        token = list ? topk_by_list<GPT, TPV>(x, top_k, P, nk, sm) : -1;
         if (token < 0) {
-          clear_selection<TPV>(sm);
+          if (list) {
+            Grp<TPV>::sync();              // the list's readers are done
+            clear_selection<TPV>(sm);
+          }
           token = select_and_draw<GPT, TPV>(sv, x, active, V, T == 0.0f, top_k, P, nk, sm, slot);
         }
       }

@@ -93,6 +93,19 @@ TOPK = [
     (1024, 4, 256, 3.6, 0.125, 40, 0.9, 0.0, 0.0),
     (1003, 4, 256, 3.6, 0.0, 30, 0.9, 0.9, -1e30),
     (130, 8, 128, 2.0, 0.0, 129, 0.99, 0.0, 0.0),
+    # the largest cut of the list and the first of the bins, for each form
+    (4096, 2, 6, 3.6, 0.0, 96, 0.9, 0.0, 0.0),
+    (4096, 2, 6, 3.6, 0.0, 97, 0.9, 0.0, 0.0),
+    (2048, 2, 6, 3.6, 0.0, 96, 1.0, 0.0, 0.0),
+    (2048, 2, 6, 3.6, 0.0, 97, 1.0, 0.0, 0.0),
+    (1024, 2, 6, 3.6, 0.0, 60, 0.9, 0.0, 0.0),
+    (1024, 2, 6, 3.6, 0.0, 61, 0.9, 0.0, 0.0),
+    (1024, 2, 6, 3.6, 0.0, 120, 1.0, 0.0, 0.0),
+    (1024, 2, 6, 3.6, 0.0, 121, 1.0, 0.0, 0.0),
+    (1024, 4, 256, 3.6, 0.0, 120, 0.9, 0.0, 0.0),
+    (1024, 4, 256, 3.6, 0.0, 121, 0.9, 0.0, 0.0),
+    (512, 4, 256, 3.6, 0.0, 511, 0.9, 0.0, 0.0),
+    (256, 4, 256, 3.6, 0.0, 255, 1.0, 0.0, 0.0),
     # masked to the lowest fp32 value, to -1e30 and to -inf; unmasked scores
     # below the first cut of the bound's search (32 under the maximum)
     (4096, 2, 6, 2.0, 0.0, 50, 0.9, 0.995, -3.4028234663852886e38),
