@@ -3,20 +3,38 @@
 // [K][F] (Sec. 2.1: stream k is offset by d_k steps, so frame f of codebook k
 // was emitted at step f + d_k).
 //
-// A thread owns one frame (de-interleave) or one step (interleave) of a request
-// and walks its K codebooks, eight loads in flight: no index division, the grid
-// side contiguous over the lanes, the stream side in whole lines (a lane's K
-// tokens are neighbours).  Bound by the launch and one memory round trip:
-// 64 requests of 1500 steps x 8 (6 MB moved) took 6.9 and 5.4 us with one
-// thread per token, which divided 64-bit indices three times.  Requests
-// shorter than a wave keep one thread per token.
+// Two forms.  A thread per token divides 64-bit indices three times, but a small
+// batch fills more of the chip with it.  A thread per frame (de-interleave) or
+// step (interleave) walks its K codebooks, eight loads in flight: no division,
+// the grid side contiguous over the lanes, the stream side in whole lines (a
+// lane's K tokens are neighbours).  Small batches are bound by the launch and one
+// memory round trip, and a thread with K tokens makes K / 8 of them.
 #include "mcd_internal.h"
 
 namespace mcd {
 namespace {
 
 constexpr int kWalk = 8;                   // codebooks in flight per thread
-constexpr int kShort = 64;                 // frames or steps below which a thread has one token
+
+// The row form's range, token form / row form in us (de-interleave of n requests
+// x F frames x K): at least a wave per request; from five codebooks on 32768
+// rows (8 x 300 x 32 2.8 / 4.7, 64 x 300 x 16 3.3 / 3.6, 64 x 700 x 16 4.4 / 4.1,
+// 256 x 700 x 16 14.0 / 8.6); three and four always (64 x 64 x 4 2.5 / 2.4, 2000 x
+// 1500 x 3 27.4 / 20.1); one and two in small batches only (64 x 64 x 1 2.42 /
+// 2.30, 2000 x 300 x 1 3.8 / 6.4, 2000 x 300 x 2 5.6 / 6.9).
+bool by_rows(int64_t n_req, int64_t len, int32_t K) {
+  if (len < 64) return false;
+  if (K <= 2) return n_req * len < 65536;
+  return K <= 4 || n_req * len >= 32768;
+}
+
+// Interleave: two codebooks from 2^20 rows on too (2000 x 700 9.9 / 9.0, 2000 x
+// 300 5.6 / 6.7), and more than eight only with 16-byte stores (2000 x 1500 x 9
+// 74.2 / 76.4, 64 x 1500 x 9 4.6 / 5.4, x 12 5.4 / 4.2).
+bool by_rows_interleave(int64_t n_req, int64_t len, int32_t K, bool vec) {
+  if (K == 2 && len >= 64 && n_req * len >= 1 << 20) return true;
+  return by_rows(n_req, len, K) && (vec || K <= 8);
+}
 
 __global__ __launch_bounds__(256) void deinterleave_rows(const int32_t *__restrict__ streams,
                                                          int32_t n_req, int32_t T, int32_t K,
@@ -103,14 +121,19 @@ __global__ __launch_bounds__(256) void interleave_kernel(const int32_t *__restri
   }
 }
 
-// One thread per frame or step: blocks of 64 threads while the batch is small,
-// so that it spreads over the compute units.
+// One thread per frame or step, in blocks of whole waves: one per request up to
+// 256; then of 64 while the batch is small, so that it spreads over the compute
+// units (64 x 1500 x 8, de-interleave: 4.0 us, with blocks of 256 4.3); else as
+// few as 256 threads allow, of equal size (2000 x 300 x 8: 19.1 us with 44 frames
+// in the second block, 13.1 with blocks of 64).
 struct RowGrid {
   dim3 grid, block;
   RowGrid(int32_t len, int32_t n_req) {
-    const unsigned nt = (int64_t)len * n_req >= 256 * 512 ? 256u : 64u;
+    const unsigned l = (unsigned)len, blocks = (l + 255) / 256;
+    const bool small = l > 256 && (int64_t)len * n_req < 131072;
+    const unsigned nt = small ? 64 : ((l + blocks - 1) / blocks + 63) / 64 * 64;
     block = dim3(nt);
-    grid = dim3(((unsigned)len + nt - 1) / nt, (unsigned)(n_req < 32768 ? n_req : 32768));
+    grid = dim3((l + nt - 1) / nt, (unsigned)(n_req < 32768 ? n_req : 32768));
   }
 };
 
@@ -126,7 +149,7 @@ hipError_t launch_deinterleave(const int32_t *streams, int32_t n_req, int32_t T,
                                const Delays &d, int32_t F, int32_t *grid, hipStream_t st) {
   const size_t total = (size_t)n_req * K * F;
   if (total == 0) return hipSuccess;
-  if (F >= kShort) {
+  if (by_rows(n_req, F, K)) {
     const RowGrid g(F, n_req);
     hipLaunchKernelGGL(deinterleave_rows, g.grid, g.block, 0, st, streams, n_req, T, K, d, F, grid);
     return hipGetLastError();
@@ -141,9 +164,10 @@ hipError_t launch_interleave(const int32_t *grid, int32_t n_req, int32_t F, int3
                              hipStream_t st) {
   const size_t total = (size_t)n_req * T * K;
   if (total == 0) return hipSuccess;
-  if (T >= kShort) {
+  const bool vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(streams) % 16 == 0;
+  if (by_rows_interleave(n_req, T, K, vec)) {
     const RowGrid g(T, n_req);
-    if (K % 4 == 0 && reinterpret_cast<uintptr_t>(streams) % 16 == 0)
+    if (vec)
       hipLaunchKernelGGL(interleave_rows<true>, g.grid, g.block, 0, st, grid, n_req, F, K, d, T,
                          pad_id, streams);
     else

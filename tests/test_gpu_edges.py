@@ -258,9 +258,10 @@ def test_two_stream_step_replayed_from_a_graph():
                                dtype="bf16", top_k=7, steps=6, shuffle=True))
 
 
-# delay pattern: one thread per token below 64 frames (steps), one per frame
-# (step) from there; codebook counts around the eight in flight and the
-# 16-byte store; large and equal delays, F = 0
+# delay pattern: one thread per token or one per frame (step), by codebooks, frames
+# per request (64) and frames in all (32768, 65536 and 2^20); codebook counts
+# around the eight in flight and the 16-byte store; request lengths around whole
+# waves and blocks; large and equal delays, F = 0
 DELAY = [
     # n_req, K, F, delays
     (3, 8, 64, range(8)),
@@ -272,6 +273,23 @@ DELAY = [
     (600, 4, 300, (0, 1, 2, 3)),
     (3, 1, 64, (5,)),
     (2, 4, 0, (0, 1, 2, 70)),
+    (512, 8, 64, range(8)),
+    (512, 3, 64, (0, 1, 0)),
+    (520, 8, 63, range(8)),
+    (511, 4, 64, (2, 0, 1, 0)),
+    (170, 7, 200, (0, 3, 3, 1, 0, 9, 2)),
+    (512, 9, 65, range(9)),
+    (256, 32, 130, range(31, -1, -1)),
+    (128, 12, 257, [100] * 12),
+    (110, 5, 301, (4, 0, 0, 1, 30)),
+    (64, 16, 513, range(16)),
+    (520, 1, 64, (5,)),
+    (1024, 1, 64, (5,)),
+    (1023, 2, 64, (1, 0)),
+    (1024, 2, 64, (1, 0)),
+    (300, 6, 700, range(6)),
+    (2100, 2, 500, (0, 5)),
+    (33000, 4, 64, (0, 1, 2, 3)),
 ]
 
 
