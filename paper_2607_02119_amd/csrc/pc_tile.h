@@ -150,10 +150,19 @@ __device__ __forceinline__ void pc_tile(const HeadView &hv, const StepView &sv, 
       const __bf16 *X = static_cast<const __bf16 *>(sv.hidden);
       // all row loads first (the copy sources and, for the epilogue, the rows
       // of a GEMM row pair per thread), then the checks
+      // Rows past the end (never stored) repeat the last one, whose lines then come
+      // from L1.  In wide tiles, several row tiles of them and enough to fill half
+      // of the chip, they go on at the first row: a last row tile with lighter loads
+      // runs ahead of its neighbours, which share its weights through L2 (200 / 130
+      // rows of 32768 columns, H 1600: 37.3 / 39.6 us with the last row, 34.7 / 34.6
+      // so; 270 of 16384 33.1 / 30.1; but 95 of 8192 in 128 x 64 tiles 11.2 / 11.9,
+      // and 200 of 4096, 32 tiles, beside 8 text rows of 8000, H 4096, 55.8 / 59.3).
+      const bool wrap = BM == 128 && BN >= 128 && tiles_m > 1 && tiles_m * ((N + BN - 1) / BN) >= 128;
       int prow[AIA];
       static_for<0, AIA>([&](auto qc) __attribute__((always_inline)) {
         constexpr int q = decltype(qc)::value;
-        prow[q] = rows[min(m0 + ((wave - 6) * AIA + q) * 8 + seg_r, M - 1)];
+        const int g = m0 + ((wave - 6) * AIA + q) * 8 + seg_r;
+        prow[q] = rows[g < M ? g : wrap ? g - M : M - 1];
       });
       const int g0 = m0 + 2 * min(q2, BM / 2 - 1);
       int pr0 = 0, pr1 = 0;
