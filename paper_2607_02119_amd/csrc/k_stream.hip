@@ -18,7 +18,7 @@ template <int BM, int BN, bool TEXT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4))) void head_gemm_pc(
     HeadView hv, StepView sv) {
   __shared__ __attribute__((aligned(1024))) char lds[PcShape<BM, BN>::kLds];
-  pc_tile<BM, BN, TEXT>(hv, sv, blockIdx.x, lds);
+  pc_tile<BM, BN, TEXT, true>(hv, sv, blockIdx.x, lds);
 }
 
 template <int BM, int BN, bool TEXT>

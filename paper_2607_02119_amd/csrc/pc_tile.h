@@ -31,8 +31,8 @@ namespace {
 template <int BM, int BN>
 struct PcShape {
   static constexpr int SK = kDmaSK, ROWB = SK * 2, NT = 512;
-  // k groups: four (every fragment is read by one wave only) up to 128
-  // accumulators per lane, else two
+  // k groups, for at most 128 accumulators per lane: four (every fragment is read
+  // by one wave only) up to 64 x 128 outputs, two up to 128 x 128, else one
   static constexpr int KSPLIT = BM * BN <= 64 * 128 ? 4 : BM * BN <= 128 * 128 ? 2 : 1;
   static constexpr int CSPLIT = 4 / KSPLIT, KS = 4 / KSPLIT;   // column groups, k16 steps per slice
   static constexpr int WN = BN / CSPLIT;                       // columns per wave
@@ -42,7 +42,8 @@ struct PcShape {
   // 32 rows: half of the LDS, so that two tiles share a compute unit and the
   // start and end of one run under the other's loop (24 text rows, 151936 x
   // 4096: 207 us at one tile per compute unit, 200 at two, 210 with 256
-  // columns; 6.2 TB/s)
+  // columns; 6.2 TB/s).  In one launch with taller audio tiles the workgroup
+  // takes their LDS, and a compute unit has one.
   static constexpr int kBudget = (BM == 32 && BN <= 128 ? 80 : 160) * 1024;
   static constexpr int SA = BN == 64 ? 3 : 2;
   static constexpr int HL = BM == 128 ? 6 : 8;   // hidden slices in flight in registers
@@ -73,7 +74,8 @@ constexpr int wide_columns(int bm) { return bm == 32 ? 128 : 256; }
 // One BM x BN tile (tile index bx: row tile bx % tiles_m, column tile
 // bx / tiles_m) with 512 threads and the workgroup's LDS buffer `lds` of
 // PcShape<BM, BN>::kLds bytes (1024-byte aligned).
-template <int BM, int BN, bool TEXT>
+// ALONE: no other tiles in the launch.
+template <int BM, int BN, bool TEXT, bool ALONE>
 __device__ __forceinline__ void pc_tile(const HeadView &hv, const StepView &sv, int bx, char *lds) {
   using S_ = PcShape<BM, BN>;
   constexpr int SK = S_::SK, MB = S_::MB, NB = S_::NB, ROWB = S_::ROWB, KS = S_::KS;
@@ -151,19 +153,30 @@ __device__ __forceinline__ void pc_tile(const HeadView &hv, const StepView &sv, 
       // all row loads first (the copy sources and, for the epilogue, the rows
       // of a GEMM row pair per thread), then the checks
       // Rows past the end (never stored) repeat the last one, whose lines then come
-      // from L1.  In wide tiles, several row tiles of them and enough to fill half
-      // of the chip, they go on at the first row: a last row tile with lighter loads
-      // runs ahead of its neighbours, which share its weights through L2 (200 / 130
-      // rows of 32768 columns, H 1600: 37.3 / 39.6 us with the last row, 34.7 / 34.6
-      // so; 270 of 16384 33.1 / 30.1; but 95 of 8192 in 128 x 64 tiles 11.2 / 11.9,
-      // and 200 of 4096, 32 tiles, beside 8 text rows of 8000, H 4096, 55.8 / 59.3).
-      const bool wrap = BM == 128 && BN >= 128 && tiles_m > 1 && tiles_m * ((N + BN - 1) / BN) >= 128;
+      // from L1.  In wide tiles, several row tiles of them and a round or two of
+      // tiles with no text rows beside, they go on at the first row: a last row
+      // tile with lighter loads runs ahead of its neighbours, which share its
+      // weights through L2 (200 / 130 rows of 32768 columns, H 1600: 37.3 / 39.6 us
+      // with the last row, 34.7 / 34.6 so; 270 of 16384 33.1 / 30.1).  Elsewhere the
+      // unit that it frees early is worth more (95 of 8192 in 128 x 64 tiles 11.2 /
+      // 11.9; beside 8 text rows of 8000 1150 of 32768, H 2048, 176.7 / 182.9).
       int prow[AIA];
-      static_for<0, AIA>([&](auto qc) __attribute__((always_inline)) {
-        constexpr int q = decltype(qc)::value;
-        const int g = m0 + ((wave - 6) * AIA + q) * 8 + seg_r;
-        prow[q] = rows[g < M ? g : wrap ? g - M : M - 1];
-      });
+      auto rows_at = [&](auto &&row) __attribute__((always_inline)) {
+        static_for<0, AIA>([&](auto qc) __attribute__((always_inline)) {
+          constexpr int q = decltype(qc)::value;
+          prow[q] = rows[row(m0 + ((wave - 6) * AIA + q) * 8 + seg_r)];
+        });
+      };
+      auto clamped = [&](int g) __attribute__((always_inline)) { return min(g, M - 1); };
+      if constexpr (ALONE && BM == 128 && BN >= 128) {
+        const int tiles = tiles_m * ((N + BN - 1) / BN);
+        if (tiles_m > 1 && tiles >= 128 && tiles <= 512 && sv.n_text == 0)
+          rows_at([&](int g) __attribute__((always_inline)) { return g < M ? g : g - M; });
+        else
+          rows_at(clamped);
+      } else {
+        rows_at(clamped);
+      }
       const int g0 = m0 + 2 * min(q2, BM / 2 - 1);
       int pr0 = 0, pr1 = 0;
       if constexpr (!TEXT) {
