@@ -1,14 +1,17 @@
-// K1 for a mixed batch in one launch: the audio rows' projection with the CFG
+// How a batch of audio and text rows runs (mixed_form), and K1 for such a batch
+// in one launch with wide audio tiles: the audio rows' projection with the CFG
 // merge and temperature (Sec. 2.1, Eq. 1, Sec. 2.4) in 256 x 256 MFMA tiles,
-// and the text rows' projection with its (max, lowest argmax) partials in
-// weight-streaming tiles (Sec. 2.4: the text head takes no CFG).
+// and the text rows' projection with its (max, lowest argmax) partials in the
+// four-wave streaming tiles of stream_tile.h (Sec. 2.4: the text head takes no
+// CFG).
 //
 // Workgroups [0, n_audio) run audio tiles, the rest text tiles.  Workgroups
 // are dispatched in index order, so the longer audio tiles start first and
 // the text tiles fill the compute units as they free up.  One launch on one
 // stream replaces two concurrent launches on two streams, and with them the
-// cross-stream fork and join of every step.  Every tile runs exactly the code
-// of its own kernel, so the results are those of the two-launch path.
+// cross-stream fork and join of every step.  Audio sums are those of the audio
+// rows alone in the same tiles; text sums agree with those of a text launch,
+// whose tiles split and walk k otherwise, within fp32 rounding.
 #include "mfma2_tile.h"
 #include "mixed_tile.h"
 
@@ -35,33 +38,51 @@ hipError_t launch_mixed(const HeadView &hv, const StepView &sv, int n_audio, hip
 
 enum class Mixed { kTwoLaunches, kStreaming, kWideAudio };
 
+// Fewer text rows (at most 64) beside many 256 x 256 audio tiles: two launches,
+// where those save more than a fork and a join cost against 128 x 256 streaming
+// tiles, in the unit of stream_cost (384 a streaming tile; a wide one 710 to 730,
+// less where H is long).
+//
+// A text part of a round or more fills the gaps of either's last round, so that
+// the tiles count and not their rounds.  Streaming tiles for both / two
+// launches, us, H 4096: 768 audio rows of 32768 columns with 64 text rows of
+// 151936 419 / 413, 1024 with 64 484 / 466, 1536 with 64 622 / 581, 1024 with 24
+// 455 / 448, 1280 with 24 527 / 516, 512 with 24 321 / 344; 896 rows, whose 256 x
+// 256 tiles are one eighth padding, with 64 429 / 450, 1800 with 24 692 / 639.  At
+// shorter H a fork and a join weigh more: 768 with 64 297 / 299 (H 2560), 1024
+// with 64 267 / 273 (H 2048) and 224 / 234 (H 1600), 1536 with 64 287 / 279 (H
+// 1600), 1800 with 24 390 / 392 (H 2048).
+//
+// A smaller one adds tiles to the last round, or a round: 1024 rows with 8 text
+// rows of 8000 275 / 308, 1536 423 / 433, 1800 527 / 506, 288 / 287 (H 2048), 2048
+// 562 / 549, 211 / 188 (H 1024); 2048 with 64 of 32003 605 / 594, 211 / 220 (H
+// 1024).
+bool two_launches(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text, int32_t H) {
+  if (n_text > 64) return false;
+  const int64_t wide = tiles_256(Mg, N), rows = tiles_128x256(Mg, N);
+  const int64_t w = H >= 3072 ? 710 : 730;
+  if (text_fills(n_text, V_text))   // two rounds of text tiles fill more than one
+    return wide * (V_text > 511 * 256 ? w : 730) < rows * 384 &&
+           (wide >= 768 || (wide >= 512 && H >= 2560) || (wide >= 384 && n_text > 32 && H >= 3072));
+  auto with_text = [](int64_t tiles, int64_t cost, int64_t text) {
+    return (tiles + 255) / 256 * cost + (tiles % 256 == 0 ? text : 0);
+  };
+  return wide >= 1024 && (n_text <= 32 || H >= 1536) &&
+         with_text(wide, w, 210) < with_text(rows, 384, 160) &&
+         mfma_tile(Mg, N, false, false).stages == 0;
+}
+
 // More than 64 text rows (one row tile of 128) beside at least one round of 256
 // x 256 audio tiles: those two in one launch.  Where the line lies (steps, H
 // 4096): 768 audio rows of 32768 columns with 128 text rows of 151936 take 455
-// us so and 465 in streaming tiles.
-//
-// Fewer text rows beside two rounds or more of 256 x 256 audio tiles: two
-// launches, where their fork and join cost less than streaming audio tiles.
-// Streaming tiles for both / two launches, us, H 4096, then H 1600 or 1024:
-// 1024 rows of 32768 columns with 64 text rows of 151936 484 / 466, 224 / 234
-// (H 1600); 1536 with 64 622 / 581, 287 / 279 (H 1600); 1024 with 24 455 / 448;
-// 512 with 24 321 / 344; 1536 with 24 593 / 564.  A text part of less than a
-// round fills no gap of the audio tiles: 1024 rows with 8 text rows of 8000 275 /
-// 308, 1536 423 / 433, 2048 562 / 549, 211 / 188 (H 1024); 2048 with 64 of 32003
-// 605 / 594, 211 / 220 (H 1024).
-//
-// Streaming tiles in one launch otherwise.
+// us so and 465 in streaming tiles.  Otherwise streaming tiles in one launch.
 Mixed mixed_form(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text, int32_t H) {
   if (Mg < 1 || n_text < 1 || n_text > 128) return Mixed::kTwoLaunches;
   const int64_t n_audio = tiles_256(Mg, N);
   if (Mg > 128 && n_text > 64 && n_audio >= 256)
     return n_audio > (1 << 20) ? Mixed::kTwoLaunches : Mixed::kWideAudio;
-  const bool fills = text_fills(n_text, V_text);
-  if (n_text <= 64 && mfma_tile(Mg, N, false, fills).stages == 0 &&
-      (fills ? n_audio >= 768 || (n_audio >= 512 && H >= 2048)
-             : n_audio >= 1024 && (n_text <= 32 || H >= 1536)))
-    return Mixed::kTwoLaunches;
-  return n_audio > (1 << 18) ? Mixed::kTwoLaunches : Mixed::kStreaming;
+  if (n_audio > (1 << 18) || two_launches(Mg, N, n_text, V_text, H)) return Mixed::kTwoLaunches;
+  return Mixed::kStreaming;
 }
 
 // Columns of the text tiles beside 256 x 256 audio tiles: narrow where 128

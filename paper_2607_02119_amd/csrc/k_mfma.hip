@@ -1,8 +1,8 @@
 // K1, MFMA-regime path (more than 128 GEMM rows): the same projection and
 // fused epilogues as the streaming path (Sec. 2.1, Eq. 1), for batches whose
 // arithmetic intensity puts them on the matrix cores: audio rows in 256 x 256
-// tiles when those fill the chip (other audio batches take the streaming
-// path's 128 x 256 tiles), text rows beyond 128 in 256 x 128 tiles.
+// tiles where their rounds cost less than streaming tiles, text rows beyond 128
+// in 256 x 128 tiles.
 #include "mfma2_tile.h"
 
 namespace mcd {
@@ -290,12 +290,13 @@ StreamTile mfma_tile(int32_t M, int32_t N, bool text, bool filled) {
   // 384; 541 against 600 for four and eight), so they win where their last
   // round is more than half full (384 tiles in two rounds 257 us, 768
   // streaming tiles in three 235).
-  // Where text tiles fill that round it is worth its tiles (1280 rows of 32768
-  // columns in 640, with 24 text rows of 151936: 521 us in streaming tiles, 498
-  // so).
+  // Where text tiles fill that round, on either side, the tiles count (1280 rows
+  // of 32768 columns in 640, with 24 text rows of 151936: 527 us in streaming
+  // tiles, 516 so).
   const int64_t tiles = tiles_256(M, N);
-  const int64_t wide = filled ? tiles * 730 / 256 : (tiles + 255) / 256 * 730;
-  return stream_cost(M, N) < wide ? stream_tile(M, N, false) : StreamTile{256, 256, 0};
+  const bool wide = filled ? tiles * 710 < tiles_128x256(M, N) * 384
+                           : (tiles + 255) / 256 * 730 <= stream_cost(M, N);
+  return wide ? StreamTile{256, 256, 0} : stream_tile(M, N, false);
 }
 
 hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text, hipStream_t st) {

@@ -14,15 +14,19 @@ inline int64_t tiles_256(int32_t M, int32_t N) {
   return (int64_t)((M + kM2Tile - 1) / kM2Tile) * ((N + kM2Tile - 1) / kM2Tile);
 }
 
+inline int64_t tiles_128x256(int32_t M, int32_t N) {   // streaming row tiles
+  return (int64_t)((M + 127) / 128) * ((N + 255) / 256);
+}
+
 // Audio rows, 256 x 256 tiles: the waves split the tile 2 x 2 (wm = wave & 1
 // row half, wn = wave >> 1 column half), each accumulating a 128 x 128 block
 // (4 x 4 blocks of v_mfma_f32_32x32x16_bf16) over both k16 halves of every
 // 32-k slice.  Per slice a workgroup copies 16 KiB of hidden states and 16 KiB
 // of weights (waves 0-1 copy weights, waves 2-3 hidden states, 8 copies each)
 // for 4 x 32 MFMAs: a third fewer bytes per MFMA than a 256 x 128 tile, and
-// half the fragment reads.  All four ring stages are in flight.  It needs at
-// least 256 tiles to fill the chip; smaller batches take the streaming path's
-// 128 x 256 row tiles.
+// half the fragment reads.  All four ring stages are in flight.  A round of 256
+// tiles takes the chip whole; batches that leave the last round half empty take
+// streaming tiles (the rule is in k_mfma.hip, for mixed batches in k_fused.hip).
 
 // LDS of one tile: the rings (or, after the loop, one 128-row half of the
 // epilogue tile) and the row-pair parameters after them.

@@ -40,15 +40,25 @@ def test_two_launches_are_reached(sizes, audio, text):
 FORMS = [
     (512, 24, 151936, 4096, 1),      # 321 / 344
     (512, 64, 151936, 4096, 1),      # 352 / 358
+    (600, 64, 151936, 4096, 1),      # 361 / 400; 256 x 256 tiles are one fifth padding
+    (768, 64, 151936, 4096, 2),      # 419 / 413
+    (768, 64, 151936, 2560, 1),      # 297 / 299
+    (768, 24, 151936, 4096, 1),      # 389 / 409
+    (896, 64, 151936, 4096, 1),      # 429 / 450; one eighth padding
     (1024, 24, 151936, 4096, 2),     # 455 / 448
     (1024, 64, 151936, 4096, 2),     # 484 / 466
+    (1024, 64, 151936, 2048, 1),     # 267 / 273
     (1024, 64, 151936, 1600, 1),     # 224 / 234
     (1280, 24, 151936, 4096, 2),     # 527 / 516
     (1536, 64, 151936, 4096, 2),     # 622 / 581
     (1536, 64, 151936, 1600, 2),     # 287 / 279
     (2048, 24, 151936, 4096, 2),     # 734 / 699
-    (640, 24, 151936, 4096, 1),      # 256 x 256 tiles would be one sixth padding
     (1024, 8, 8000, 4096, 1),        # 275 / 308
+    (1800, 24, 151936, 4096, 2),     # 692 / 639
+    (1800, 24, 151936, 2048, 1),     # 390 / 392
+    (1800, 8, 8000, 4096, 2),        # 527 / 506
+    (1800, 8, 8000, 2048, 1),        # 288 / 287
+    (2304, 8, 8000, 4096, 1),        # the text tiles fill the last round of 256 x 256 tiles only
     (2048, 8, 8000, 4096, 2),        # 562 / 549
     (2048, 8, 8000, 1024, 2),        # 211 / 188
     (2048, 64, 32003, 1024, 1),      # 211 / 220
