@@ -41,34 +41,35 @@ enum class Mixed { kTwoLaunches, kStreaming, kWideAudio };
 // Fewer text rows (at most 64) beside many 256 x 256 audio tiles: two launches,
 // where those save more than a fork and a join cost against 128 x 256 streaming
 // tiles, in the unit of stream_cost (384 a streaming tile; a wide one 710 to 730,
-// less where H is long).
+// less where H is long and its prologue and epilogue weigh less).
 //
 // A text part of a round or more fills the gaps of either's last round, so that
 // the tiles count and not their rounds.  Streaming tiles for both / two
-// launches, us, H 4096: 768 audio rows of 32768 columns with 64 text rows of
-// 151936 419 / 413, 1024 with 64 484 / 466, 1536 with 64 622 / 581, 1024 with 24
-// 455 / 448, 1280 with 24 527 / 516, 512 with 24 321 / 344; 896 rows, whose 256 x
-// 256 tiles are one eighth padding, with 64 429 / 450, 1800 with 24 692 / 639.  At
-// shorter H a fork and a join weigh more: 768 with 64 297 / 299 (H 2560), 1024
-// with 64 267 / 273 (H 2048) and 224 / 234 (H 1600), 1536 with 64 287 / 279 (H
-// 1600), 1800 with 24 390 / 392 (H 2048).
+// launches, us, audio rows of 32768 columns, text rows of 151936: H 4096, 768
+// with 64 419 / 413, 1024 with 64 484 / 466, 1536 with 64 622 / 581, 1024 with 24
+// 455 / 448, 1280 with 24 527 / 516, 1800 with 24 692 / 653, 512 with 24 321 / 344,
+// 896 with 64, whose 256 x 256 tiles are one eighth padding, 429 / 450.  H 2560:
+// 768 with 64 297 / 299, 1664 with 24 450 / 429.  H 2048: 1024 with 64 267 / 273,
+// 1664 with 24 351 / 350, 1800 with 24 385 / 366.  H 1600: 1024 with 64 224 / 234,
+// 1536 with 64 287 / 279, 1664 with 24 293 / 298, 1800 with 24 326 / 311.
 //
-// A smaller one adds tiles to the last round, or a round: 1024 rows with 8 text
-// rows of 8000 275 / 308, 1536 423 / 433, 1800 527 / 506, 288 / 287 (H 2048), 2048
-// 562 / 549, 211 / 188 (H 1024); 2048 with 64 of 32003 605 / 594, 211 / 220 (H
-// 1024).
+// A smaller one adds tiles to the last round, or a round.  With 8 text rows of
+// 8000: 1024 rows 275 / 308, 1536 423 / 433, 1800 524 / 495, 2048 562 / 549; 1800 at
+// H 2560 388 / 357, at H 2048 295 / 300; 2432 at H 1600 323 / 318, at H 1024
+// 222 / 233; 2048 at H 1024 211 / 188.  2048 with 64 of 32003 605 / 594, at H 1024 211 / 220.
 bool two_launches(int32_t Mg, int32_t N, int32_t n_text, int32_t V_text, int32_t H) {
   if (n_text > 64) return false;
   const int64_t wide = tiles_256(Mg, N), rows = tiles_128x256(Mg, N);
-  const int64_t w = H >= 3072 ? 710 : 730;
-  if (text_fills(n_text, V_text))   // two rounds of text tiles fill more than one
-    return wide * (V_text > 511 * 256 ? w : 730) < rows * 384 &&
+  if (text_fills(n_text, V_text)) {   // two rounds of text tiles fill more than one
+    const int64_t w = V_text <= 511 * 256 ? 730 : H >= 2048 ? 710 : 718;
+    return wide * w < rows * 384 &&
            (wide >= 768 || (wide >= 512 && H >= 2560) || (wide >= 384 && n_text > 32 && H >= 3072));
+  }
   auto with_text = [](int64_t tiles, int64_t cost, int64_t text) {
     return (tiles + 255) / 256 * cost + (tiles % 256 == 0 ? text : 0);
   };
   return wide >= 1024 && (n_text <= 32 || H >= 1536) &&
-         with_text(wide, w, 210) < with_text(rows, 384, 160) &&
+         with_text(wide, H >= 2560 ? 710 : H >= 1536 ? 722 : 730, 210) < with_text(rows, 384, 160) &&
          mfma_tile(Mg, N, false, false).stages == 0;
 }
 

@@ -55,9 +55,15 @@ FORMS = [
     (2048, 24, 151936, 4096, 2),     # 734 / 699
     (1024, 8, 8000, 4096, 1),        # 275 / 308
     (1800, 24, 151936, 4096, 2),     # 692 / 639
-    (1800, 24, 151936, 2048, 1),     # 390 / 392
-    (1800, 8, 8000, 4096, 2),        # 527 / 506
-    (1800, 8, 8000, 2048, 1),        # 288 / 287
+    (1664, 24, 151936, 2560, 2),     # 450 / 429
+    (1664, 24, 151936, 1600, 1),     # 293 / 298
+    (1800, 24, 151936, 2048, 2),     # 385 / 366
+    (1800, 24, 151936, 1600, 2),     # 326 / 311
+    (1800, 8, 8000, 4096, 2),        # 524 / 495
+    (1800, 8, 8000, 2560, 2),        # 388 / 357
+    (1800, 8, 8000, 2048, 1),        # 295 / 300
+    (2432, 8, 8000, 1600, 2),        # 323 / 318
+    (2432, 8, 8000, 1024, 1),        # 222 / 233
     (2304, 8, 8000, 4096, 1),        # the text tiles fill the last round of 256 x 256 tiles only
     (2048, 8, 8000, 4096, 2),        # 562 / 549
     (2048, 8, 8000, 1024, 2),        # 211 / 188
