@@ -175,9 +175,9 @@ typedef struct {
 /* The whole hot path of one step: projection + merge + temperature (scores),
  * text-head greedy argmax, selection, draw, pads, companion copy, grid scatter.
  * Equal to mcd_head_logits followed by mcd_sample_step: kernel launches on
- * `stream` (a batch with both audio and text rows also runs the text
- * projection on a second stream of the head, forked from and joined back to
- * `stream`); no device allocation, no synchronisation. */
+ * `stream` (for some batches with both audio and text rows the text
+ * projection runs on a second stream of the head, forked from and joined back
+ * to `stream`); no device allocation, no synchronisation. */
 mcd_status mcd_head_step(const mcd_head *head, const mcd_step_args *args, hipStream_t stream);
 
 /* ---- allocation-free step ---------------------------------------------------

@@ -8,9 +8,10 @@
 //   solo row j:  scores[n_pairs + j][n] = l / T;  T = 0 (greedy): no division
 //   text rows:   per row and 32-column part, the largest logit and its lowest id.
 //
-// bf16 heads run on the streaming kernel (k_stream.hip) up to 128 GEMM rows and
-// on the MFMA-regime kernel (k_mfma.hip) above; fp32 heads (true fp32
-// products) run on the fp32 matrix instruction here.
+// bf16 heads run on the streaming kernel (k_stream.hip) up to 128 GEMM rows;
+// above, audio rows there too or in 256 x 256 tiles, whichever costs less, and
+// text rows in 256 x 128 tiles (k_mfma.hip).  fp32 heads (true fp32 products)
+// run on the fp32 matrix instruction here.
 #include "gemm_common.h"
 
 namespace mcd {

@@ -18,9 +18,9 @@
 struct mcd_head {
   mcd::HeadView hv;
   int32_t max_delay;
-  // Batches with both audio and text rows run the two projections
-  // concurrently: the text part on a second stream of the head, forked from
-  // and joined back to the caller's stream with events.  Created with the
+  // Batches with both audio and text rows that are not one launch run the two
+  // projections concurrently: the text part on a second stream of the head,
+  // forked from and joined back to the caller's stream with events.  Created with the
   // head (bf16 heads with a text head), so a step creates nothing; the mutex
   // orders the event records of concurrent steps on one head.
   mutable std::mutex side_mu;
@@ -368,10 +368,10 @@ size_t mcd_workspace_bytes(const mcd_head *h, int32_t R) {
 
 namespace {
 
-// K1 for one batch.  Audio and text rows together: one launch of both up to
-// 128 text rows, else the audio projection on the caller's stream
-// and the text projection on the head's second stream, both after everything
-// already on the caller's stream, which waits for both.
+// K1 for one batch.  Audio and text rows together: one launch of both (mostly,
+// up to 128 text rows: launch_mixed_gemm), else the audio projection on the
+// caller's stream and the text projection on the head's second stream, both
+// after everything already on the caller's stream, which waits for both.
 hipError_t run_head_gemm(const mcd_head *h, const mcd::StepView &sv, hipStream_t stream) {
   if (h->hv.dtype != MCD_BF16 || sv.Mg == 0 || sv.n_text == 0)
     return mcd::launch_head_gemm(h->hv, sv, stream);

@@ -97,8 +97,8 @@ inline bool text_fills(int32_t n_text, int32_t V_text) {
 }
 hipError_t launch_mfma_gemm(const HeadView &hv, const StepView &sv, bool text,
                             hipStream_t stream);     // any number of rows
-// A batch of audio rows and at most 128 text rows: both projections in one
-// launch; *launched is false (and nothing is launched) for other batches.
+// Both projections of a batch of audio and text rows in one launch; *launched is
+// false (and nothing is launched) for the batches that take two.
 hipError_t launch_mixed_gemm(const HeadView &hv, const StepView &sv, hipStream_t st,
                              bool *launched);
 // How a bf16 step's projections run: launches (0 to 2) and the tiles of its parts.

@@ -15,13 +15,14 @@ namespace {
 // global -> LDS, non-temporal, SW stages deep; waves 6-7 load the hidden rows
 // into registers HL slices ahead and write them to a ring of SA stages.
 //
-// What bounds the loop is the number of bytes in flight: hidden rows come from
-// L2, but behind the weights' HBM reads in the compute unit's in-order return
-// path, so every byte takes 1.5 - 2 us under load, and a rate of 100 GB/s per
-// compute unit needs 150 - 200 KiB under way, more than the LDS holds.  The
-// registers of the loading waves hold the hidden rows' part of it, the LDS the
-// weights' part; neither costs the computing waves a stall, where a
-// wave that also computes adds its copies and LDS writes to its MFMAs.
+// The buffers are sized by bytes in flight: hidden rows come from L2, but behind
+// the weights' HBM reads in the compute unit's in-order return path, so every
+// byte takes 1.5 - 2 us under load, and 100 GB/s per compute unit would need 150 -
+// 200 KiB under way.  The registers of the loading waves hold the hidden rows'
+// part of it, the LDS the weights' part; neither costs the computing waves a
+// stall, where a wave that also computes adds its copies and LDS writes to its
+// MFMAs.  The loops take in 42 - 50 GB/s with about that much under way, so
+// this is not all that bounds them.
 //
 // The computing waves split a slice by columns and k: KSPLIT k groups of
 // 4 / KSPLIT column groups.  One barrier per slice: at the barrier of slice st,

@@ -1,12 +1,12 @@
-// Streaming tile of the mixed launch's text rows (at most 128, beside 256 x 256
-// audio tiles): the text-head projection with a fused (max, lowest argmax)
-// epilogue,
+// Four-wave streaming tile of the text rows (65 to 128) that share a launch with
+// 256 x 256 audio tiles: the text-head projection with a fused (max, lowest
+// argmax) epilogue,
 //
 //   logits[g][n] = sum_h hidden[row(g)][h] * W_text[n][h]
 //   per row and 32-column part, the largest logit and its lowest id.
 //
-// The streaming launches proper take the eight-wave tile of pc_tile.h, which
-// shares the LDS layout and the waits defined here.
+// All other streaming tiles are the eight-wave ones of pc_tile.h, which share
+// the LDS layout and the waits defined here.
 #pragma once
 
 #include "gemm_common.h"
@@ -25,10 +25,10 @@ namespace {
 // end) or, for 256-column tiles, 4 x 1 (column quarter, all of k).
 //
 // Every byte a compute unit takes in, from HBM or from L2, crosses the L2 ->
-// CU path, and that path (about 45-50 GB/s per CU measured) bounds the loop:
-// the hidden states are re-read by every column tile, as many bytes per tile
-// as its weights when BM = BN.  Wide tiles (BN = 256) halve that share; they
-// are used when there is more than one round of 128-column tiles.
+// CU path, and the loop takes in 45-50 GB/s per unit: the hidden states are
+// re-read by every column tile, as many bytes per tile as its weights when
+// BM = BN.  Wide tiles (BN = 256) halve that share; they are used when there is
+// more than one round of 128-column tiles.
 //
 // LDS layout of a slice: [rows][8 chunks of 16 B]; chunk c of row r is stored
 // at position c ^ ((r >> 1) & 7), so the 16 rows of an MFMA fragment read hit
@@ -55,8 +55,7 @@ __device__ __forceinline__ void wait_slices(int ahead) {
   });
 }
 
-// Tile shape of the streaming path, shared by its kernel and by the fused
-// mixed-batch kernel (which sizes its LDS buffer from kLds).
+// Tile shape; the mixed launch sizes its LDS buffer from kLds.
 template <int BM, int BN>
 struct DmaShape {
   static constexpr int SK = kDmaSK;

@@ -105,7 +105,7 @@ RAGGED = [
                                dtype="bf16", top_k=7, temperature=0.7, steps=6, shuffle=True)),
     ("bf16_topp_two_tiles", dict(H=192, K=2, V=333, n_pairs=20, n_solo=3, dtype="bf16",
                                  top_p=0.9, cfg_w=2.0, steps=4)),
-    # H % 256 == 0 and at most 128 rows: the weight-streaming kernel (32/64/128-row tiles)
+    # at most 128 rows: streaming tiles of 32, 64 and 128 rows and 64 columns, audio and text
     ("stream_bm32_text", dict(H=256, K=3, V=37, n_pairs=10, n_solo=5, n_text=3, V_text=300,
                               dtype="bf16", top_k=7, temperature=0.7, steps=5, shuffle=True)),
     ("stream_bm64", dict(H=512, K=2, V=333, n_pairs=25, n_solo=3, n_text=40, V_text=1000,
@@ -124,16 +124,16 @@ RAGGED = [
                       top_k=5, top_p=0.8, steps=5, shuffle=True, bias=True)),
     ("stream_bm128", dict(H=768, K=4, V=129, n_pairs=55, n_solo=3, n_text=100, V_text=515,
                           dtype="bf16", top_k=20, steps=5)),
-    # more than one round of 128-column tiles: 256-column streaming tiles with
-    # a ragged last tile (audio: 64-row tiles, N % 4 != 0; text: 32-row tiles)
+    # more than one round of 128-column tiles: wide streaming tiles with a ragged
+    # last tile (audio: 64 x 256, N % 4 != 0; text: 32 x 128)
     ("stream_wide_bm64", dict(H=128, K=9, V=3739, n_pairs=20, n_solo=3, n_text=5, V_text=33000,
                               dtype="bf16", top_k=20, temperature=0.9, steps=10, shuffle=True)),
-    # 128-row 256-column tiles, fewer slices than weight stages (H = 192)
+    # 128 x 256 tiles for both parts, fewer slices than weight stages (H = 192)
     ("stream_wide_bm128", dict(H=192, K=9, V=3700, n_pairs=60, n_solo=5, n_text=100,
                                V_text=40000, dtype="bf16", top_p=0.9, cfg_w=2.5, steps=10)),
     # streams of unequal size (one large stream and smaller ones): the
-    # streaming kernel with N % 4 != 0, 128-row streaming tiles, and the
-    # one-wave-per-vector sampler
+    # streaming kernel with N % 4 != 0, 128 x 128 streaming tiles in two row
+    # tiles, and the one-wave-per-vector sampler
     ("unequal_streams_stream", dict(H=128, K=4, V=100, V_stream=(100, 37, 64, 5), n_pairs=6,
                                     n_solo=2, n_text=2, V_text=300, dtype="bf16", top_k=7,
                                     temperature=0.8, steps=6, shuffle=True, bias=True)),
@@ -155,12 +155,12 @@ RAGGED = [
                              T_text=64, dtype="bf16", top_k=15, steps=9, shuffle=True)),
     ("text_mask_f32", dict(H=40, K=3, V=37, n_pairs=3, n_solo=2, n_text=4, V_text=70,
                            T_text=32, dtype="f32", top_k=5, steps=4, shuffle=True)),
-    # more than 128 audio rows and fewer than 256 tiles of 256 x 256: 128 x 256
-    # streaming tiles, row tile by row tile (here three, the last one ragged)
+    # more than 128 audio rows of few columns: 32 x 64 streaming tiles, row tile
+    # by row tile (here ten, the last one ragged)
     ("rows_three_row_tiles", dict(H=128, K=3, V=100, n_pairs=150, n_solo=7, dtype="bf16", top_k=10,
                                 temperature=0.9, steps=4, shuffle=True)),
-    # 2 x 4 and 3 x 8 tiles of 128 x 256 (the second with a ragged row tile):
-    # the XCD-aware order
+    # 8 x 16 tiles of 32 x 64 and 5 x 32 of 64 x 64 (the second with a ragged row
+    # tile): the XCD-aware order
     ("rows_xcd_remap", dict(H=192, K=4, V=256, n_pairs=100, n_solo=56, dtype="bf16", top_p=0.9,
                             cfg_w=2.5, steps=4)),
     ("rows_xcd_remap_ragged", dict(H=256, K=4, V=512, n_pairs=140, n_solo=20, dtype="bf16",
@@ -181,9 +181,9 @@ RAGGED = [
                                      shuffle=True)),
     ("mfma_text_rows", dict(H=128, K=2, V=40, n_pairs=3, n_solo=2, n_text=150, V_text=300,
                             dtype="bf16", top_k=5, steps=3, shuffle=True)),
-    # streaming tiles that never straddle two streams (V a multiple of the
-    # 64-, 128- and 256-column tile widths), every draw path; a small p so that
-    # the first candidate often falls outside the nucleus
+    # streaming tiles that never straddle two streams (V a multiple of the 64- and
+    # 128-column tile widths), every draw path; a small p so that the first
+    # candidate often falls outside the nucleus
     ("aligned_topp_bn64", dict(H=256, K=3, V=256, n_pairs=20, n_solo=7, dtype="bf16", top_p=0.9,
                             cfg_w=2.5, steps=6, shuffle=True)),
     ("aligned_small_p", dict(H=128, K=4, V=512, n_pairs=9, n_solo=6, dtype="bf16", top_p=0.3,
