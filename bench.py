@@ -54,8 +54,8 @@ MEASURED_TRAFFIC = {
     # workload: dict(sources=[...], sha256=..., fetch_bytes=..., write_bytes=..., profile=...)
     "weight_streaming": dict(
         sources=["k_stream.hip", "pc_tile.h", "stream_tile.h", "gemm_common.h"],
-        sha256="29b0352b3b2e035e65774b85691acb4a12159f8286036adf646d3b6d2ab4e83e",
-        fetch_bytes=277099520, write_bytes=8388608,
+        sha256="6a84b55fbbc36b9022b8bb88fb5d56df3fa50170b0e4f1bf787e203c4df10981",
+        fetch_bytes=277103616, write_bytes=8388608,
         profile="profiles/head_step_weight_streaming.md"),
 }
 
